@@ -146,31 +146,85 @@ __global__ __launch_bounds__(kThreads) void k_frame_init(int B, uint64_t *minmax
   if (i < 6 * B) minmax[i] = (i % 6) < 3 ? ~0ull : 0ull;
 }
 
-__global__ __launch_bounds__(kThreads) void k_frame_reduce(const BoxDev *boxes, int B, uint32_t n,
-                                                           uint64_t *minmax, uint32_t *status) {
-  uint32_t g = blockIdx.x * kThreads + threadIdx.x;
-  if (g >= n) return;
-  int b = box_of(boxes, B, g);
-  const BoxDev &bx = boxes[b];
-  if (bx.periodic) return;
-  uint32_t i = g - bx.p_off;
-  const double *x = bx.pos + 3ull * i;
-  bool ok = true;
-  uint64_t o[3];
+// Bounding cube of the open boxes.  One atomic per particle and bound, all
+// on the same six words, ran at 11 ns each whatever the size (6.8 ms for 1e5
+// particles); here a workgroup takes a run of `tile` particles, reduces the
+// run of each box in it in registers and issues one set of six atomics per
+// box and workgroup (per box and wave where the run spans several boxes):
+// build + force of 1e5 isolated particles 9.09 -> 2.25 ms.  The minima and maxima are of integers, so
+// the result does not depend on the order.
+struct Extent {
+  uint64_t o[6];  // smallest and largest ordered coordinates
+  __device__ void clear() {
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    double v = x[k];
-    ok = ok && isfinite(v);
-    o[k] = d2ord(v);
+    for (int k = 0; k < 6; ++k) o[k] = k < 3 ? ~0ull : 0ull;
   }
-  if (!ok) {
-    atomicOr(status, kStatusRange);
+  __device__ void take(int k, uint64_t v) {
+    if (k < 3) o[k] = v < o[k] ? v : o[k];
+    else o[k] = v > o[k] ? v : o[k];
+  }
+  __device__ void add(const double *x, uint32_t *status) {
+    if (!(isfinite(x[0]) && isfinite(x[1]) && isfinite(x[2]))) {
+      atomicOr(status, kStatusRange);
+      return;
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const uint64_t v = d2ord(x[k]);
+      take(k, v);
+      take(k + 3, v);
+    }
+  }
+  __device__ void reduce_wave() {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+      for (int k = 0; k < 6; ++k) take(k, __shfl_xor((unsigned long long)o[k], off, 64));
+  }
+  __device__ void store(uint64_t *mm) const {
+    if (o[3] < o[0]) return;  // no finite particle
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      atomicMin((unsigned long long *)&mm[k], (unsigned long long)o[k]);
+      atomicMax((unsigned long long *)&mm[3 + k], (unsigned long long)o[3 + k]);
+    }
+  }
+};
+
+__global__ __launch_bounds__(kThreads) void k_frame_reduce(const BoxDev *boxes, int B, uint32_t n, uint32_t tile,
+                                                           uint64_t *minmax, uint32_t *status) {
+  __shared__ Extent part[kWaves];
+  const uint32_t base = blockIdx.x * tile, end = min(n, base + tile);
+  if (base >= n) return;
+  const int b0 = box_of(boxes, B, base), b1 = box_of(boxes, B, end - 1);
+  const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
+  if (b0 == b1) {
+    const BoxDev &bx = boxes[b0];
+    if (bx.periodic) return;
+    Extent e;
+    e.clear();
+    for (uint32_t g = base + threadIdx.x; g < end; g += kThreads) e.add(bx.pos + 3ull * (g - bx.p_off), status);
+    e.reduce_wave();
+    if (lane == 0) part[w] = e;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+      for (int v = 1; v < kWaves; ++v)
+#pragma unroll
+        for (int k = 0; k < 6; ++k) e.take(k, part[v].o[k]);
+      e.store(minmax + 6 * b0);
+    }
     return;
   }
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    atomicMin((unsigned long long *)&minmax[6 * b + k], (unsigned long long)o[k]);
-    atomicMax((unsigned long long *)&minmax[6 * b + 3 + k], (unsigned long long)o[k]);
+  for (int b = b0 + (int)w; b <= b1; b += kWaves) {  // a wave per box
+    const BoxDev &bx = boxes[b];
+    if (bx.periodic) continue;
+    const uint32_t g1 = min(end, bx.p_off + bx.n);
+    Extent e;
+    e.clear();
+    for (uint32_t g = max(base, bx.p_off) + lane; g < g1; g += 64) e.add(bx.pos + 3ull * (g - bx.p_off), status);
+    e.reduce_wave();
+    if (lane == 0) e.store(minmax + 6 * b);
   }
 }
 
@@ -1115,7 +1169,9 @@ void launch_build(BuildArrays &A, hipStream_t s) {
   k_init_scalars<<<1, 64, 0, s>>>(A.scalars, n, A.top_cnt);
   if (A.any_open) {
     k_frame_init<<<cdiv(6 * (uint64_t)A.B, kThreads), kThreads, 0, s>>>(A.B, A.minmax);
-    k_frame_reduce<<<nb, kThreads, 0, s>>>(A.boxes, A.B, n, A.minmax, &A.scalars[0]);
+    // at most 256 workgroups: 1536 atomics on one box's six words
+    const uint32_t tile = std::max<uint32_t>(2048, cdiv(n, 256));
+    k_frame_reduce<<<cdiv(n, tile), kThreads, 0, s>>>(A.boxes, A.B, n, tile, A.minmax, &A.scalars[0]);
     k_frame_finalize<<<cdiv(A.B, 64), 64, 0, s>>>(A.boxes, A.B, A.minmax);
   }
   // Start in the buffer pair that makes the sorted result land in *_a.
