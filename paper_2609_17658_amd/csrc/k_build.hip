@@ -1094,8 +1094,8 @@ __global__ __launch_bounds__(kThreads) void k_max_level(const Topo *topo, const 
 }
 
 __global__ void k_reset(uint32_t *w) { *w = 0; }
-__global__ void k_reset_n(uint32_t *w, int n) {
-  if ((int)threadIdx.x < n) w[threadIdx.x] = 0;
+__global__ void k_reset_queues(uint32_t *counter) {
+  if (threadIdx.x < kQueues) counter[threadIdx.x * kQueueStride] = 0;
 }
 // Status word cleared, particle count for the device-side scans, counters
 // of the top-node lists cleared.
@@ -1126,7 +1126,7 @@ int device_cu_count() {
 }
 
 void launch_reset(uint32_t *word, hipStream_t s) { k_reset<<<1, 1, 0, s>>>(word); }
-void launch_reset_n(uint32_t *words, int n, hipStream_t s) { k_reset_n<<<1, 64, 0, s>>>(words, n); }
+void launch_reset_queues(uint32_t *counter, hipStream_t s) { k_reset_queues<<<1, 64, 0, s>>>(counter); }
 
 void launch_max_level(const BuildArrays &A, uint32_t *out, hipStream_t s) {
   k_reset<<<1, 1, 0, s>>>(out);

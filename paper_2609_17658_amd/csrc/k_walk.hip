@@ -179,26 +179,41 @@ __device__ inline void write_out(const WalkArgs &A, const BoxDev &bx, uint32_t s
 // share its tree nodes in their L2.  A wave whose range is exhausted moves
 // on to the next range, so every group is processed exactly once and every
 // wave leaves the loop once all ranges are exhausted.
+// A device-scope atomic takes about 11 ns on its line whoever asks, so the
+// counters stand on lines of their own, and a wave whose range is exhausted
+// reads all the counters at once (lane q reads counter q) and takes its next
+// atomic only on a range that still holds groups: the last wave of a launch
+// leaves after one read instead of eight atomics in a row (1e5 active of 1e6
+// particles 2.55 -> 1.99 ms, a 64^3 TreePM step 1.38 -> 1.21 ms, 2M
+// particles 5.92 -> 5.88 ms).
 struct GroupQueue {
   uint32_t *counters;
   uint32_t n_groups;
-  uint32_t q, tried;
+  uint32_t q, done;  // done: ranges this wave has found exhausted (bit mask)
 };
 __device__ inline uint32_t range_begin(uint32_t n_groups, uint32_t q) {
   return (uint32_t)(((uint64_t)n_groups * q) / kQueues);
 }
 // Next group for this wave, or n_groups when all are taken.
 __device__ inline uint32_t pop_group(GroupQueue &Q, uint32_t lane) {
-  while (Q.tried < kQueues) {
+  while (true) {
     const uint32_t b = range_begin(Q.n_groups, Q.q), e = range_begin(Q.n_groups, Q.q + 1);
     uint32_t i = 0;
-    if (lane == 0) i = atomicAdd(&Q.counters[Q.q], 1u);
+    if (lane == 0) i = atomicAdd(&Q.counters[Q.q * kQueueStride], 1u);
     i = __builtin_amdgcn_readlane(i, 0);  // wave-uniform
     if (b + i < e) return b + i;
-    Q.q = (Q.q + 1) % kQueues;
-    ++Q.tried;
+    Q.done |= 1u << Q.q;  // each range is tried at most once more than it holds groups
+    bool left = false;
+    if (lane < kQueues) {
+      const uint32_t c = __hip_atomic_load(&Q.counters[lane * kQueueStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      left = c < range_begin(Q.n_groups, lane + 1) - range_begin(Q.n_groups, lane);
+    }
+    const uint32_t open = (uint32_t)__ballot(left) & ~Q.done;
+    if (!open) return Q.n_groups;
+    // the next open range after q, cyclically
+    const uint32_t after = open & ~((2u << Q.q) - 1u);
+    Q.q = (uint32_t)__builtin_ctz(after ? after : open);
   }
-  return Q.n_groups;
 }
 // Target and group counts produced on the device (active targets).
 __device__ inline void device_counts(WalkArgs &A) {
@@ -212,7 +227,7 @@ __device__ inline GroupQueue make_queue(const WalkArgs &A) {
   Q.counters = A.counter;
   Q.n_groups = A.n_groups;
   Q.q = blockIdx.x % kQueues;
-  Q.tried = 0;
+  Q.done = 0;
   return Q;
 }
 
@@ -1812,7 +1827,7 @@ void launch_walk(const WalkArgs &W0, int precision, hipStream_t s) {
   W.no_interior = env_flag("OG_NO_INTERIOR") ? 1 : 0;
   const uint32_t cus = (uint32_t)device_cu_count();
   const uint32_t groups = W.n_groups > 0 ? W.n_groups : 1;
-  launch_reset_n(W.counter, kQueues, s);
+  launch_reset_queues(W.counter, s);
   if (W.group_lists) {
     if (precision == 0) {
       const uint32_t blocks = std::max<uint32_t>(1, std::min<uint32_t>(3u * cus, (groups + 3) / 4));

@@ -126,7 +126,7 @@ void carve(Carver &c, BuildArrays &A, uint32_t n, uint32_t node_cap, int B, bool
   A.top_cnt = c.take<uint32_t>(32);
   A.top_buf = c.take<uint32_t>(kTopWords * A.top_cap);
   A.top_id = c.take<uint32_t>(node_cap);
-  A.scalars = c.take<uint32_t>(32);
+  A.scalars = c.take<uint32_t>(kScalarWords);
   if (soft) {
     A.seps = c.take<double>(n);
     A.semax = c.take<double>(node_cap);
@@ -319,7 +319,7 @@ WalkArgs Forest::walk_args() const {
     if (kind(b) != W.box_kind) W.box_kind = 0;
     if (b.spline || b.relative) W.ext = 1;
   }
-  W.counter = &A.scalars[8];
+  W.counter = &A.scalars[32];
   W.group_lists = group_lists;
   W.seps = A.seps;
   W.semax = A.semax;
@@ -360,7 +360,7 @@ size_t subset_plan(TargetArrays &T, uint32_t M, char *base) {
   T.tval_b = c.take<uint32_t>(M);
   T.hist = c.take<uint32_t>(radix_hist_words(M));
   T.digit_tot = c.take<uint32_t>(256);
-  T.scalars = c.take<uint32_t>(32);
+  T.scalars = c.take<uint32_t>(kScalarWords);
   return c.off + 256;
 }
 
@@ -374,7 +374,7 @@ int Forest::walk_subset_in(int prec, hipStream_t s, const int64_t *idx, uint32_t
   WalkArgs W = walk_args();
   W.n_groups = (M + group_max - 1) / group_max;
   W.n_targets = M;
-  W.counter = &T.scalars[8];
+  W.counter = &T.scalars[32];
   W.tkey = T.tkey;
   W.tval = T.tval;
   W.acc = acc;
@@ -413,7 +413,7 @@ int Forest::walk_active(int prec, hipStream_t s, const int8_t *bin, int32_t leve
     T.partial = cv.take<uint32_t>(scan_partial_words(N));
     T.tkey = cv.take<uint64_t>(N);
     T.tval = cv.take<uint32_t>(N);
-    T.counts = cv.take<uint32_t>(32);
+    T.counts = cv.take<uint32_t>(kScalarWords);
   };
   Carver c;
   plan(c);
@@ -433,7 +433,7 @@ int Forest::walk_active(int prec, hipStream_t s, const int8_t *bin, int32_t leve
   W.n_groups = (N + group_max - 1) / group_max;  // bound for the grid; the count is read on the device
   W.n_targets = N;
   W.dev_count = T.counts;
-  W.counter = &T.counts[8];
+  W.counter = &T.counts[32];
   W.tkey = T.tkey;
   W.tval = T.tval;
   W.acc = acc;
@@ -501,7 +501,7 @@ constexpr uint32_t kNoAllocTargets = OG_NOALLOC_MAX_TARGETS;
 constexpr size_t noalloc_align(size_t x) { return (x + 255) & ~(size_t)255; }
 // the sizes subset_plan carves for M targets, each 256-byte aligned
 constexpr size_t noalloc_bytes(size_t M) {
-  const size_t parts[7] = {8 * M, 8 * M, 4 * M, 4 * M, 4 * 256 * ((M + kSortTile - 1) / kSortTile), 4 * 256, 4 * 32};
+  const size_t parts[7] = {8 * M, 8 * M, 4 * M, 4 * M, 4 * 256 * ((M + kSortTile - 1) / kSortTile), 4 * 256, 4 * kScalarWords};
   size_t off = 0;
   for (size_t p : parts) off = noalloc_align(off) + p;
   return off + 256;

@@ -47,7 +47,7 @@ struct BuildArrays {
   uint32_t *top_buf;          // TopArrays' lists, kTopWords per top node (top_cap)
   uint32_t *top_id;           // per node: index of a top node in the top list
   uint32_t top_cap;           // bound on the top nodes (top_node_bound)
-  uint32_t *scalars;          // [0] status [3] n_nodes [4] n [8..15] walk queues
+  uint32_t *scalars;          // [0] status [3] n_nodes [4] n [32..] walk queues (kScalarWords in all)
                               // [5] deepest level (stats)
   int any_open;               // some box has periodic = 0
   int leaf_max;               // largest leaf_max of the boxes
@@ -70,6 +70,11 @@ struct TopArrays {
   uint32_t *id;     // per node (node_cap): its class (a top node: with its index in `list`)
   uint32_t cap;
 };
+// Walk group queues: one per XCD (see k_walk.hip), each counter on a cache
+// line of its own, after the 32 status and count words.
+constexpr uint32_t kQueues = 8, kQueueStride = 32;
+constexpr uint32_t kScalarWords = 32 + kQueues * kQueueStride;
+
 constexpr size_t kTopWords = 20;  // words of top_buf per top node
 
 void launch_build(BuildArrays &A, hipStream_t s);
@@ -83,7 +88,7 @@ struct TargetArrays {
   uint64_t *tkey_a, *tkey_b;
   uint32_t *tval_a, *tval_b;
   uint32_t *hist, *digit_tot;
-  uint32_t *scalars;          // [0] status [8..15] walk queues
+  uint32_t *scalars;          // [0] status [32..] walk queues (kScalarWords in all)
   const uint64_t *tkey;       // result (points at a or b)
   const uint32_t *tval;
 };
@@ -99,7 +104,7 @@ struct ActiveArrays {
   uint32_t *flags, *offs, *partial;
   uint64_t *tkey;
   uint32_t *tval;
-  uint32_t *counts;           // [0] active, [1] groups, [8..15] walk queues
+  uint32_t *counts;           // [0] active, [1] groups, [32..] walk queues (kScalarWords in all)
   int64_t *n_active;
 };
 void launch_active(const BuildArrays &A, ActiveArrays &T, uint32_t chunk, hipStream_t s);
@@ -123,7 +128,7 @@ struct WalkArgs {
   int B;                      // boxes
   int box_kind;               // shared by all boxes: 1 cutoff+open, 2 cutoff+periodic,
                               // 3 Newtonian+open; 0 mixed
-  uint32_t *counter;          // kQueues group counters
+  uint32_t *counter;          // kQueues group counters, kQueueStride words apart
   const uint64_t *tkey;       // sorted target positions, or null: all particles
   const uint32_t *tval;       // target slots
   double *acc;                // non-null: outputs by slot; null: per-box acc/pot
@@ -141,10 +146,7 @@ struct WalkArgs {
 };
 void launch_walk(const WalkArgs &W, int precision, hipStream_t s);
 void launch_reset(uint32_t *word, hipStream_t s);
-void launch_reset_n(uint32_t *words, int n, hipStream_t s);
-
-// Walk group queues: one per XCD (see k_walk.hip).
-constexpr uint32_t kQueues = 8;
+void launch_reset_queues(uint32_t *counter, hipStream_t s);
 
 int device_cu_count();
 
