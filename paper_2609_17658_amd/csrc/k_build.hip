@@ -505,14 +505,16 @@ __global__ __launch_bounds__(kThreads) void k_lcp_depth(const BoxDev *boxes, int
 
 // Per box: node range [S[p_off], S[p_off+n]).
 // Node range of each box; a box's root has no parent.
+// The roots take the first B child slots (see k_links).
 __global__ void k_box_nodes(BoxDev *boxes, int B, const uint32_t *S, uint32_t n, uint32_t node_cap,
-                            uint32_t *scalars, uint32_t *parent) {
+                            uint32_t *scalars, uint32_t *parent, uint32_t *sib) {
   int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b < B) {
     const uint32_t root = min(S[boxes[b].p_off], node_cap);
     boxes[b].root = root;
     boxes[b].node_end = min(S[boxes[b].p_off + boxes[b].n], node_cap);
     if (root < node_cap) parent[root] = 0xffffffffu;
+    if ((uint32_t)b < node_cap) sib[b] = root;
   }
   if (b == 0) {
     uint32_t tot = S[n];
@@ -576,21 +578,49 @@ __global__ __launch_bounds__(kThreads) void k_emit(const BoxDev *boxes, int B, u
   }
 }
 
-// Parent links: every child of an internal node points at it.
-__global__ __launch_bounds__(kThreads) void k_links(const Topo *topo, const uint32_t *skip,
-                                                    const uint32_t *scalars, uint32_t node_cap,
-                                                    uint32_t *parent) {
+// Parent links (every child of an internal node points at it) and child
+// slots: the children of node r stand in consecutive entries of sib, from
+// kid[r] >> 3, in child order, (kid[r] & 7) + 1 of them, so that lanes can
+// take a node's children side by side where the skip chain gives one after
+// another.  A workgroup reserves the slots of its nodes with one atomic; the
+// order of the reservations shows only in the slot numbers.
+__global__ __launch_bounds__(kThreads) void k_links(const Topo *topo, const uint32_t *skip, const uint32_t *scalars,
+                                                    uint32_t node_cap, uint32_t *parent, uint32_t *kid, uint32_t *sib,
+                                                    uint32_t *slots) {
+  __shared__ uint32_t tmp[kWaves], s_base;
   const uint32_t tot = min(scalars[3], node_cap);
-  for (uint32_t r = blockIdx.x * kThreads + threadIdx.x; r < tot; r += gridDim.x * kThreads) {
-    const Topo t = topo[r];
-    if (t.corner & kLeafBit) continue;
-    const uint32_t end = min(t.a, tot);
-    for (uint32_t c = r + 1; c < end;) {
-      parent[c] = r;
-      const uint32_t nx = skip[c];
-      if (nx <= c) break;  // never taken for a well-formed tree
-      c = nx;
+  for (uint32_t r0 = blockIdx.x * kThreads; r0 < tot; r0 += gridDim.x * kThreads) {
+    const uint32_t r = r0 + threadIdx.x;
+    uint32_t ch[8], k = 0;
+    if (r < tot) {
+      const Topo t = topo[r];
+      if (!(t.corner & kLeafBit)) {
+        const uint32_t end = min(t.a, tot);
+        uint32_t c = r + 1;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          ch[q] = c;
+          if (c < end) {
+            k = q + 1;
+            parent[c] = r;
+            const uint32_t nx = skip[c];
+            c = nx > c ? nx : end;  // a skip always moves forward in a well-formed tree
+          }
+        }
+      }
     }
+    uint32_t total;
+    const uint32_t at = block_exscan<true>(k, tmp, &total);
+    if (threadIdx.x == 0) s_base = total ? atomicAdd(slots, total) : 0u;
+    lds_barrier();
+    const uint32_t base = s_base + at;
+    if (k && base + k <= node_cap) {
+      kid[r] = base << 3 | (k - 1u);
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if ((uint32_t)q < k) sib[base + q] = ch[q];
+    }
+    lds_barrier();  // s_base is read before the next round sets it
   }
 }
 
@@ -1098,13 +1128,13 @@ __global__ void k_reset_queues(uint32_t *counter) {
   if (threadIdx.x < kQueues) counter[threadIdx.x * kQueueStride] = 0;
 }
 // Status word cleared, particle count for the device-side scans, counters
-// of the top-node lists cleared.
-__global__ void k_init_scalars(uint32_t *sc, uint32_t n, uint32_t *top_cnt) {
+// of the top-node lists cleared, child slots from B on (the roots' come first).
+__global__ void k_init_scalars(uint32_t *sc, uint32_t n, uint32_t *top_cnt, int B) {
   if (threadIdx.x == 0) {
     sc[0] = 0u;
     sc[4] = n;
   }
-  if (threadIdx.x < 4) top_cnt[threadIdx.x] = 0;
+  if (threadIdx.x < 4) top_cnt[threadIdx.x] = threadIdx.x == 1 ? (uint32_t)B : 0u;
 }
 
 inline uint32_t cdiv(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b); }
@@ -1166,7 +1196,7 @@ bool radix_sort(uint64_t *keys_a, uint32_t *vals_a, uint64_t *keys_b, uint32_t *
 void launch_build(BuildArrays &A, hipStream_t s) {
   const uint32_t n = A.n;
   const uint32_t nb = cdiv(n, kThreads);
-  k_init_scalars<<<1, 64, 0, s>>>(A.scalars, n, A.top_cnt);
+  k_init_scalars<<<1, 64, 0, s>>>(A.scalars, n, A.top_cnt, A.B);
   if (A.any_open) {
     k_frame_init<<<cdiv(6 * (uint64_t)A.B, kThreads), kThreads, 0, s>>>(A.B, A.minmax);
     // at most 256 workgroups: 1536 atomics on one box's six words
@@ -1198,10 +1228,10 @@ void launch_build(BuildArrays &A, hipStream_t s) {
     k_lcp_depth<<<nb, kThreads, kThreads + 2 * A.leaf_max + 1, s>>>(A.boxes, A.B, n, A.leaf_max, skeys, A.lcp,
                                                                     A.depth, A.nstart);
     scan_u32(A.nstart, A.S, &A.scalars[4], n, A.scan_partial, s);
-    k_box_nodes<<<cdiv(A.B, 64), 64, 0, s>>>(A.boxes, A.B, A.S, n, A.node_cap, A.scalars, A.parent);
+    k_box_nodes<<<cdiv(A.B, 64), 64, 0, s>>>(A.boxes, A.B, A.S, n, A.node_cap, A.scalars, A.parent, A.sib);
     k_emit<<<nb, kThreads, 0, s>>>(A.boxes, A.B, n, skeys, A.lcp, A.depth, A.S, A.node_cap, A.topo,
                                    A.first, A.skip);
-    k_links<<<gnodes, kThreads, 0, s>>>(A.topo, A.skip, A.scalars, A.node_cap, A.parent);
+    k_links<<<gnodes, kThreads, 0, s>>>(A.topo, A.skip, A.scalars, A.node_cap, A.parent, A.kid, A.sib, A.top_cnt + 1);
   }
   {
     const TraceRange r("build: moments");

@@ -215,11 +215,15 @@ __device__ inline uint32_t pop_group(GroupQueue &Q, uint32_t lane) {
     Q.q = (uint32_t)__builtin_ctz(after ? after : open);
   }
 }
-// Target and group counts produced on the device (active targets).
+// Target and group counts produced on the device (active targets).  Lists of
+// up to small_max targets belong to the eight-lane walk (kSmall), longer ones
+// to the others: of the two launched, one finds nothing to do.
+template <bool kSmall = false>
 __device__ inline void device_counts(WalkArgs &A) {
   if (A.dev_count) {
     A.n_targets = cptr(A.dev_count)[0];
     A.n_groups = cptr(A.dev_count)[1];
+    if ((A.n_targets <= A.small_max) != kSmall) A.n_groups = 0;
   }
 }
 __device__ inline GroupQueue make_queue(const WalkArgs &A) {
@@ -577,6 +581,7 @@ __global__ __launch_bounds__(64 * kWalk64Waves) __attribute__((amdgpu_waves_per_
   double(*lsoft)[64] = lsofts[kExt ? wv : 0];
   double4 *slots = slotss[wv];
   device_counts(A);
+  if (A.n_groups == 0) return;
   GroupQueue Q = make_queue(A);
   while (true) {
     const uint32_t g = pop_group(Q, lane);
@@ -748,14 +753,12 @@ __device__ inline void spline32(float u, float hinv, float &g, float &w) {
   }
 }
 
-// One partner at offset (dx, dy, dz) with r2 = |d|^2, mass m: FP32 pair
-// term, accumulated in FP64.
+// FP32 pair term of a partner at distance^2 r2 and G times mass gm (walk
+// records and FP32 particle copies hold the product): the force factor fs =
+// G m (1/r^3) S and the potential ps = G m (1/r) erfc, softened.
 // e: the pair's softening length when k.soft (kExt variants only).
 template <bool kExt>
-// gm: the partner's G times mass (walk records and FP32 particle copies hold
-// it so).
-__device__ inline void eval32(float dx, float dy, float dz, float r2, float gm, const Consts32 &k, double &ax,
-                              double &ay, double &az, double &ph, float e = 0.0f) {
+__device__ inline void terms32(float r2, float gm, const Consts32 &k, float e, float &fs, float &ps) {
 #pragma clang fp contract(fast)
   float g, wv;  // softened 1/r^3 and 1/r
   if (kExt && k.spline) {
@@ -791,7 +794,6 @@ __device__ inline void eval32(float dx, float dy, float dz, float r2, float gm, 
     S = ec + kTwoOverSqrtPiV * v * e;
     pf = ec;
   }
-  float fs, ps;  // G m (1/r^3) S and G m (1/r) erfc, softened
   if (kExt && k.spline) {
     fs = gm * g * S;
     ps = gm * wv * pf;
@@ -800,6 +802,16 @@ __device__ inline void eval32(float dx, float dy, float dz, float r2, float gm, 
     ps = gw * pf;
     fs = gw * (wv * wv) * S;
   }
+}
+
+// One partner at offset (dx, dy, dz) with r2 = |d|^2: its FP32 pair term,
+// accumulated in FP64 (the product of the FP32 factor and offset is exact).
+template <bool kExt>
+__device__ inline void eval32(float dx, float dy, float dz, float r2, float gm, const Consts32 &k, double &ax,
+                              double &ay, double &az, double &ph, float e = 0.0f) {
+#pragma clang fp contract(fast)
+  float fs, ps;
+  terms32<kExt>(r2, gm, k, e, fs, ps);
   const double f = (double)fs;
   ax = fma(f, (double)dx, ax);
   ay = fma(f, (double)dy, ay);
@@ -819,6 +831,31 @@ __device__ inline int wrap_cells(int d) {
 __device__ inline float wrap_box(float d, const Consts32 &k) {
   const float hi = d > k.half_box ? d - k.box : d;
   return d < -k.half_box ? d + k.box : hi;
+}
+
+// Lane origin of target p at q: the centre of its level-21 cell, in
+// half-cells, and its FP32 offset from it.  One function for the mixed walks,
+// so that its rounding is theirs.
+__device__ inline void lane_origin(const WalkArgs &A, const BoxDev &bx, uint32_t p, const double4 &q, int &o0, int &o1,
+                                   int &o2, float &xr, float &yr, float &zr) {
+#pragma clang fp contract(fast)
+  uint32_t cc[3];
+  key_cell(A.skeys[p], bx.curve, cc);
+  o0 = 2 * (int)cc[0] + 1;
+  o1 = 2 * (int)cc[1] + 1;
+  o2 = 2 * (int)cc[2] + 1;
+  const double h22 = bx.L * 0x1p-22;
+  xr = (float)(q.x - (bx.lo[0] + (double)o0 * h22));
+  yr = (float)(q.y - (bx.lo[1] + (double)o1 * h22));
+  zr = (float)(q.z - (bx.lo[2] + (double)o2 * h22));
+}
+
+// alpha |a_old| of target p of box bx, as the mixed walks' relative criterion
+// takes it.
+__device__ inline float alpha_aold(const WalkArgs &A, const BoxDev &bx, uint32_t p) {
+#pragma clang fp contract(fast)
+  const double *v = A.a_old + 3ull * (A.perm[p] - bx.p_off);
+  return (float)(bx.alpha * sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]));
 }
 
 __device__ inline int wave_max_i32(int v) {
@@ -916,6 +953,7 @@ __attribute__((amdgpu_waves_per_eu(kCap == 4 ? 8 : 1, 8))) void k_walk32(WalkArg
   __shared__ float lsoft[kSoft ? kCap : 1][kWalk32Threads];  // monopoles' softening lengths
   const uint32_t lane = threadIdx.x;
   device_counts(A);
+  if (A.n_groups == 0) return;
   GroupQueue Q = make_queue(A);
   while (true) {
     const uint32_t g = pop_group(Q, lane);
@@ -946,25 +984,11 @@ __attribute__((amdgpu_waves_per_eu(kCap == 4 ? 8 : 1, 8))) void k_walk32(WalkArg
     // relative criterion: open iff G M side^2 > alpha |a_old| r^4 (the
     // record's mass is G M)
     float aol = 0.0f;
-    if (relative && valid) {
-      const double *v = A.a_old + 3ull * (A.perm[p] - bx.p_off);
-      aol = (float)(bx.alpha * sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]));
-    }
+    if (relative && valid) aol = alpha_aold(A, bx, p);
     // lane origin: centre of the target's level-21 cell, in half-cells
     int o0 = 0, o1 = 0, o2 = 0;
     float xr = 0.0f, yr = 0.0f, zr = 0.0f;
-    if (valid) {
-      uint32_t cc[3];
-      key_cell(A.skeys[p], bx.curve, cc);
-      o0 = 2 * (int)cc[0] + 1;
-      o1 = 2 * (int)cc[1] + 1;
-      o2 = 2 * (int)cc[2] + 1;
-      const double h22 = bx.L * 0x1p-22;
-      const double4 q = A.part64[p];
-      xr = (float)(q.x - (bx.lo[0] + (double)o0 * h22));
-      yr = (float)(q.y - (bx.lo[1] + (double)o1 * h22));
-      zr = (float)(q.z - (bx.lo[2] + (double)o2 * h22));
-    }
+    if (valid) lane_origin(A, bx, p, A.part64[p], o0, o1, o2, xr, yr, zr);
     // Offsets between a lane's origin o and a node centre c, in half-cells.
     // Periodic box (2^22 half-cells): with g the first lane's origin and
     // E = max |o - g| over the group's lanes, the scalar unit reduces c - g
@@ -1256,6 +1280,7 @@ __global__ __launch_bounds__(kWalk32Threads) __attribute__((amdgpu_waves_per_eu(
   __shared__ double4 slots[kWalk32Threads];
   const uint32_t lane = threadIdx.x;
   device_counts(A);
+  if (A.n_groups == 0) return;
   GroupQueue Q = make_queue(A);
   while (true) {
     const uint32_t g = pop_group(Q, lane);
@@ -1466,6 +1491,384 @@ __global__ __launch_bounds__(kWalk32Threads) __attribute__((amdgpu_waves_per_eu(
   }
 }
 
+// -------------------------------------------------- eight lanes per target --
+// The walks above advance one node at a time for 64 targets: a chain of some
+// hundred to thousands of dependent steps (record load, tests, list append),
+// 0.3-0.5 us each when few waves share a SIMD.  A launch of few targets is
+// bound by that chain (one target of a 2M tree: 670 us), and targets that lie
+// far apart make it longer still, as a wave follows the union of its lanes'
+// walks.  This walk gives each target eight lanes, which take the children of
+// a node side by side (k_links keeps them in consecutive slots): a step tests
+// up to eight siblings, so the chain is the number of nodes the target opens,
+// and a launch has eight times the waves.  It reads every record with vector
+// loads, one per target, so it costs more per target than the 64-target walks
+// once the chip is full: the launch rule stands at launch_walk.
+//
+// Order: the siblings up to the first opened one give their entries (accepted
+// monopoles, opened leaves) in child order, the others wait on a stack (their
+// run of slots and a mask) until that one's subtree is done, so entries enter
+// the target's queue in traversal order.  A full queue is evaluated eight
+// partners at a time: each lane forms one partner's terms, and lanes 0..3 add
+// the eight terms of one component each, one after another.  The terms are
+// those of the 64-target walks and each target adds them in the same order
+// (the product of an FP32 factor and offset is exact in FP64, so adding it is
+// the fused multiply-add of eval32): the results are the same to the bit.
+constexpr uint32_t kLanes8 = 8, kQueue8 = 32, kStack8 = kLevels + 3;
+
+// Value of the lane k places below within the group of eight (0 past its end).
+template <int k>
+__device__ inline uint32_t below8(uint32_t v, uint32_t l8) {
+  const uint32_t t = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x110 + k, 0xf, 0xf, false);  // row_shr:k
+  return l8 >= (uint32_t)k ? t : 0u;
+}
+__device__ inline uint32_t incl_scan8(uint32_t v, uint32_t l8) {
+  v += below8<1>(v, l8);
+  v += below8<2>(v, l8);
+  return v + below8<4>(v, l8);
+}
+// OR over the group of eight: quad_perm [1,0,3,2], [2,3,0,1], row_half_mirror.
+__device__ inline uint32_t or8(uint32_t v) {
+  v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, false);
+  v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, false);
+  return v | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, false);
+}
+
+// This group's eight bits of a ballot.
+__device__ inline uint32_t bits8(bool v, uint32_t lane) {
+  const uint64_t b = __ballot(v);
+  return __builtin_amdgcn_ubfe(lane < 32u ? (uint32_t)b : (uint32_t)(b >> 32), lane & 24u, 8u);
+}
+// Element i of an array of fewer than 2^32 bytes: a 32-bit byte offset on a
+// uniform base.
+template <class T>
+__device__ inline T at32(const T *p, uint32_t i) {
+  return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(p) + (uint32_t)(i * (uint32_t)sizeof(T)));
+}
+
+template <bool kFp64, bool kExt, bool kTail>
+__global__ __launch_bounds__(64) void k_walk8(WalkArgs A) {
+#pragma clang fp contract(off)
+  // queue entries: partner (mixed: offset and G m, or offset of the leaf's
+  // centre of mass and first particle; FP64: node or first particle), and
+  // the particle count of a leaf (0: a monopole) with kEWrap
+  __shared__ float4 q32[kFp64 ? 1 : kLanes8][kFp64 ? 1 : kQueue8];
+  __shared__ uint32_t q64[kFp64 ? kLanes8 : 1][kFp64 ? kQueue8 : 1];
+  __shared__ uint32_t qn[kLanes8][kQueue8];
+  __shared__ float qsoft[kExt && !kFp64 ? kLanes8 : 1][kExt && !kFp64 ? kQueue8 : 1];  // monopoles' lengths
+  __shared__ uint2 stack[kLanes8][kStack8];  // runs of siblings that wait: first slot, mask
+  __shared__ __attribute__((aligned(16))) double terms[64][4];
+  const uint32_t lane = threadIdx.x, l8 = lane & 7u, sub = lane >> 3, base = lane & 56u;
+  device_counts<true>(A);
+  if (A.n_groups == 0) return;
+  // runs of eight targets: of a list or a single box as they come, of a
+  // batch's walk groups (up to 64 targets of one box)
+  const bool one = A.tkey != nullptr || A.B == 1;
+  const uint32_t runs = (A.chunk + kLanes8 - 1) / kLanes8;
+  GroupQueue Q = make_queue(A);
+  Q.n_groups = one ? (A.n_targets + kLanes8 - 1) / kLanes8 : A.n_groups * runs;
+  while (true) {
+    const uint32_t gi = pop_group(Q, lane);
+    if (gi >= Q.n_groups) break;
+    GroupRef gr;
+    if (one) {
+      gr.box = 0;
+      gr.tstart = gi * kLanes8;
+      gr.tcount = min(kLanes8, A.n_targets - gr.tstart);
+    } else {
+      gr = group_of(A, gi / runs);
+      const uint32_t before = min(gi % runs * kLanes8, gr.tcount);
+      gr.tstart += before;
+      gr.tcount = min(kLanes8, gr.tcount - before);
+      if (gr.tcount == 0) continue;
+    }
+    const BoxDev bx = ld(A.boxes + gr.box);
+    const bool cut = bx.cutoff != 0, per = bx.periodic != 0, relative = kExt && bx.relative;
+    // offsets of exactly half the box have two images; below this cutoff they
+    // are pruned in either
+    const bool half_reach = !(bx.rcut <= 0.25 * bx.box);
+    const bool soft = kExt && A.seps != nullptr && bx.epsp != nullptr;
+    uint32_t p = 0, slot = 0;
+    const bool valid = lane_target(A, gr, bx, sub, p, slot);
+    double4 xi = make_double4(0.0, 0.0, 0.0, 0.0);
+    if (valid) xi = A.part64[p];
+    const double ei = soft && valid ? A.seps[p] : bx.eps;
+    double aold = 0.0;
+    if (kFp64 && relative && valid) aold = norm3_64(A.a_old + 3ull * (A.perm[p] - bx.p_off));
+    // the mixed walk's constants, lane origin and offset from it
+    Consts32 k;
+    float eif = 0.0f, aol = 0.0f, xr = 0.0f, yr = 0.0f, zr = 0.0f;
+    int o0 = 0, o1 = 0, o2 = 0;
+    if (!kFp64) {
+      k.G = bx.Gf;
+      k.eps2 = bx.eps2f;
+      k.inv2rs = bx.inv2rsf * kSqrtLog2e;
+      k.rc2 = bx.rc2f;
+      k.theta2 = bx.theta2f;
+      k.h22 = bx.h22f;
+      k.box = bx.Lf;
+      k.half_box = 0.5f * bx.Lf;
+      k.cutoff = cut;
+      k.periodic = per;
+      k.spline = kExt && bx.spline;
+      k.hs2 = bx.hsf * bx.hsf;
+      k.hinv = bx.hinvf;
+      k.soft = soft;
+      eif = (float)ei;
+      if (relative && valid) aol = alpha_aold(A, bx, p);
+      if (valid) lane_origin(A, bx, p, xi, o0, o1, o2, xr, yr, zr);
+    }
+    // every lane of a group of eight holds the same run (the siblings being
+    // tested), stack depth and queue state
+    uint2 run = make_uint2(gr.box, valid ? 1u : 0u);  // the roots hold slots 0 .. B-1
+    uint32_t sp = 0, qh = 0, ql = 0, off = 0;         // off: items taken of the queue's first entry
+    double sum = 0.0;  // lanes 0..3: ax, ay, az, potential
+    uint32_t ni = 0;
+    // Evaluate up to eight items (a monopole, or one particle of a leaf) of
+    // each queue; a queue of fewer waits unless this is the last of it.
+    auto round = [&](bool last) __attribute__((always_inline)) {
+      const uint32_t at = (qh + l8) & (kQueue8 - 1);
+      const bool have = l8 < ql;
+      uint32_t items = 0;
+      if (have) {
+        const uint32_t c = qn[sub][at] & kCountMask;
+        items = (c ? c : 1u) - (l8 == 0 ? off : 0u);
+      }
+      const uint32_t incl = incl_scan8(items, l8), excl = incl - items;
+      const uint32_t total = (uint32_t)__shfl((int)incl, (int)(lane | 7u), 64);
+      uint32_t take = min(kLanes8, total);
+      if (take < kLanes8 && !last) take = 0;
+      // the entries' first items as a bit mask: item l8 belongs to the entry
+      // whose bit is the highest at or below l8
+      const uint32_t starts = or8(have && excl < kLanes8 ? 1u << excl : 0u);
+      double t0 = 0.0, t1 = 0.0, t2 = 0.0, t3 = 0.0;
+      if (l8 < take) {
+        const uint32_t upto = starts & ((2u << l8) - 1u);
+        const uint32_t en = (uint32_t)__builtin_popcount(upto) - 1u;
+        const uint32_t j = l8 - (31u - (uint32_t)__builtin_clz(upto)) + (en == 0 ? off : 0u);
+        const uint32_t ea = (qh + en) & (kQueue8 - 1);
+        const uint32_t c = qn[sub][ea];
+        if (!kFp64) {
+#pragma clang fp contract(fast)
+          const float4 q = q32[sub][ea];
+          float dx = q.x, dy = q.y, dz = q.z, m = q.w, r2, es = 0.0f;
+          bool use = true;
+          if (c & kCountMask) {
+            const uint32_t i = __float_as_uint(q.w) + j;
+            const float4 pq = at32(A.part32, i);
+            // the first eight of a leaf are placed from the image of its
+            // centre of mass, as the 64-target walk places them
+            if ((c & kEWrap) && j < 8u) {
+              dx = wrap_box(dx, k);
+              dy = wrap_box(dy, k);
+              dz = wrap_box(dz, k);
+            }
+            dx += pq.x;
+            dy += pq.y;
+            dz += pq.z;
+            if (c & kEWrap) {
+              dx = wrap_box(dx, k);
+              dy = wrap_box(dy, k);
+              dz = wrap_box(dz, k);
+            }
+            m = pq.w;
+            r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+            use = i != p && (!cut || r2 < k.rc2);
+            if (kExt && soft) {
+              const float ej = (float)A.seps[i];
+              es = eif > ej ? eif : ej;
+            }
+          } else {
+            r2 = fmaf(dz, dz, fmaf(dx, dx, dy * dy));
+            if (kExt && soft) es = qsoft[sub][ea];
+          }
+          if (use) {
+            float fs, ps;
+            terms32<kExt>(r2, m, k, es, fs, ps);
+            const double f = (double)fs;
+            t0 = f * (double)dx;
+            t1 = f * (double)dy;
+            t2 = f * (double)dz;
+            t3 = -(double)ps;
+            ++ni;
+          }
+        } else {
+          const uint32_t ref = q64[sub][ea];
+          double dx, dy, dz, m, es = bx.eps;
+          bool use = true;
+          if (c & kCountMask) {
+            const uint32_t i = ref + j;
+            use = i != p;
+            const double4 s = at32(A.part64, i);
+            dx = s.x - xi.x;
+            dy = s.y - xi.y;
+            dz = s.z - xi.z;
+            m = s.w;
+            if (soft) {
+              const double ej = A.seps[i];
+              es = ei > ej ? ei : ej;
+            }
+          } else {
+            const Mom64 mm = at32(A.mom64, ref);
+            dx = mm.cx - xi.x;
+            dy = mm.cy - xi.y;
+            dz = mm.cz - xi.z;
+            m = mm.m;
+            if (soft) {
+              const double emax = A.semax[ref];
+              es = ei > emax ? ei : emax;
+            }
+          }
+          minimg3(dx, dy, dz, per, bx.box);
+          double4 t;
+          if (use && pair64_terms<kExt, kTail>(dx, dy, dz, m, es, bx, t)) {
+            t0 = t.x;
+            t1 = t.y;
+            t2 = t.z;
+            t3 = -t.w;
+            ++ni;
+          }
+        }
+      }
+      // a partner that does not contribute adds zeros, which change no sum
+      *reinterpret_cast<double2 *>(&terms[lane][0]) = make_double2(t0, t1);
+      *reinterpret_cast<double2 *>(&terms[lane][2]) = make_double2(t2, t3);
+      __builtin_amdgcn_wave_barrier();
+      if (l8 < 4) {
+#pragma unroll
+        for (uint32_t i = 0; i < kLanes8; ++i) sum += terms[base + i][l8];
+      }
+      __builtin_amdgcn_wave_barrier();
+      // entries used up, and the items taken of the next one
+      const uint32_t full = bits8(have && incl <= take, lane);
+      const uint32_t nf = (uint32_t)__builtin_popcount(full);
+      const uint32_t upto = (uint32_t)__shfl((int)incl, (int)(base + (nf ? nf - 1u : 0u)), 64);
+      off = nf ? take - upto : off + take;
+      qh = (qh + nf) & (kQueue8 - 1);
+      ql -= nf;
+    };
+    while (__ballot(run.y != 0)) {
+      // room for the eight entries a step may add
+      if (__ballot(ql > kQueue8 - kLanes8)) {
+        do round(false);
+        while (__ballot(ql > kQueue8 / 2));
+      }
+      const bool has = (run.y >> l8) & 1u;
+      uint32_t node = 0, kw = 0, a = 0, cnt = 0;
+      bool leaf = false, live = false, open = false, within = false;
+      float dx = 0.0f, dy = 0.0f, dz = 0.0f, gm = 0.0f, emono = 0.0f;
+      uint32_t wrapf = 0;
+      if (has) {
+        node = at32(A.sib, run.x + l8);
+        kw = at32(A.kid, node);
+        if (!kFp64) {
+#pragma clang fp contract(fast)
+          const WNode w = at32(A.wnode, node);
+          float f0, f1, f2;
+          if (per && !half_reach) {
+            // the difference modulo 2^22, as a signed field
+            f0 = (float)(int)__builtin_amdgcn_sbfe(w.c[0] - o0, 0, 22);
+            f1 = (float)(int)__builtin_amdgcn_sbfe(w.c[1] - o1, 0, 22);
+            f2 = (float)(int)__builtin_amdgcn_sbfe(w.c[2] - o2, 0, 22);
+          } else if (per) {
+            constexpr int kMask = (1 << 22) - 1;
+            f0 = (float)wrap_cells((w.c[0] & kMask) - o0);
+            f1 = (float)wrap_cells((w.c[1] & kMask) - o1);
+            f2 = (float)wrap_cells((w.c[2] & kMask) - o2);
+          } else {
+            f0 = __int_as_float(w.c[0]) - biased(o0);
+            f1 = __int_as_float(w.c[1]) - biased(o1);
+            f2 = __int_as_float(w.c[2]) - biased(o2);
+          }
+          const float dcx = f0 * k.h22 - xr, dcy = f1 * k.h22 - yr, dcz = f2 * k.h22 - zr;
+          const float mdc = fmaxf(fmaxf(fabsf(dcx), fabsf(dcy)), fabsf(dcz));
+          leaf = (w.cf & kWLeaf) != 0;
+          cnt = w.cf & kWCount;
+          a = w.a & kTagFirst;
+          const bool wrapd = per && (w.cf & kWWrap) != 0;
+          wrapf = wrapd ? kEWrap : 0u;
+          dx = dcx + w.o[0];
+          dy = dcy + w.o[1];
+          dz = dcz + w.o[2];
+          const float ux = dx, uy = dy, uz = dz;
+          if (wrapd) {
+            dx = wrap_box(dx, k);
+            dy = wrap_box(dy, k);
+            dz = wrap_box(dz, k);
+          }
+          gm = w.m;
+          const float r2 = fmaf(dz, dz, fmaf(dx, dx, dy * dy));
+          live = !(cut && mdc > w.reach);
+          const bool far_open = relative ? (w.m * w.side2 > aol * (r2 * r2)) : (w.side2 > r2);
+          open = far_open || (mdc < w.near);
+          if (kExt && soft) {
+            const float emax = (float)A.semax[node], emin = (float)A.semin[node];
+            const float hm = 2.8f * emax;
+            if (emin < emax && emax > eif && r2 < hm * hm) open = true;
+            emono = eif > emax ? eif : emax;
+          }
+          within = !cut || r2 < k.rc2;
+          if (open) {  // a leaf's entry holds its centre of mass as it is
+            dx = ux;
+            dy = uy;
+            dz = uz;
+          }
+        } else {
+          const Topo t = at32(A.topo, node);
+          leaf = (t.corner & kLeafBit) != 0;
+          cnt = t.b & kCountMask;
+          a = t.a;
+          bool pruned;
+          tests64(at32(A.cen64, node), at32(A.mom64, node), xi, per, bx, relative, aold, soft, soft ? A.semin[node] : 0.0,
+                  soft ? A.semax[node] : 0.0, ei, pruned, open, within);
+          live = !pruned;
+        }
+      }
+      // the first sibling opened to its children ends this step's siblings
+      const uint32_t opened = bits8(live && open && !leaf, lane);
+      const uint32_t e = opened ? (uint32_t)__builtin_ctz(opened) : kLanes8;
+      const bool entry = live && l8 < e && (open ? leaf : within);
+      const uint32_t em = bits8(entry, lane);
+      if (entry) {
+        const uint32_t at = (qh + ql + (uint32_t)__builtin_popcount(em & ((1u << l8) - 1u))) & (kQueue8 - 1);
+        qn[sub][at] = open ? cnt | wrapf : 0u;
+        if (kFp64) q64[sub][at] = open ? a : node;
+        else q32[sub][at] = make_float4(dx, dy, dz, open ? __uint_as_float(a) : gm);
+        if (kExt && !kFp64 && soft) qsoft[sub][at] = emono;
+      }
+      ql += (uint32_t)__builtin_popcount(em);
+      // later siblings that give something wait; the opened one's children are next
+      const uint32_t want = bits8(live && (open || within), lane);
+      const uint32_t kids = (uint32_t)__shfl((int)kw, (int)(base + (e & 7u)), 64);
+      if (e < kLanes8) {
+        const uint32_t rest = want & ~((2u << e) - 1u);
+        if (rest) {
+          if (l8 == 0) stack[sub][sp] = make_uint2(run.x, rest);
+          ++sp;
+        }
+        run = make_uint2(kids >> 3, (2u << (kids & 7u)) - 1u);
+      } else if (sp) {
+        --sp;
+        __builtin_amdgcn_wave_barrier();
+        run = stack[sub][sp];
+      } else {
+        run.y = 0;
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    while (__ballot(ql != 0)) round(true);
+    uint32_t n8 = ni;
+#pragma unroll
+    for (int d = 1; d < 8; d <<= 1) n8 += (uint32_t)__shfl_xor((int)n8, d, 64);
+    if (valid) {
+      double *acc = A.acc ? A.acc : bx.acc;
+      double *pot = A.pot_override ? A.pot : bx.pot;
+      if (l8 < 3) acc[3ull * slot + l8] = sum;
+      else if (l8 == 3 && pot) pot[slot] = sum;
+      else if (l8 == 4 && A.nint) A.nint[slot] = (int64_t)n8;
+    }
+  }
+}
+
 // ------------------------------------------- group-shared interaction lists --
 // One walk per group of targets (the paper's grouped neighbour search
 // applied to the tree walk): at a visited node every lane applies the
@@ -1484,6 +1887,7 @@ __global__ __launch_bounds__(256) void k_walkg64(WalkArgs A) {
 #pragma clang fp contract(off)
   const uint32_t lane = threadIdx.x & 63;
   device_counts(A);
+  if (A.n_groups == 0) return;
   GroupQueue Q = make_queue(A);
   while (true) {
     const uint32_t g = pop_group(Q, lane);
@@ -1608,6 +2012,7 @@ __global__ __launch_bounds__(kWalk32Threads) __attribute__((amdgpu_waves_per_eu(
   __shared__ GEntry list[kGroupCap];
   const uint32_t lane = threadIdx.x;
   device_counts(A);
+  if (A.n_groups == 0) return;
   GroupQueue Q = make_queue(A);
   while (true) {
     const uint32_t g = pop_group(Q, lane);
@@ -1635,24 +2040,10 @@ __global__ __launch_bounds__(kWalk32Threads) __attribute__((amdgpu_waves_per_eu(
     uint32_t p = 0, slot = 0;
     const bool valid = lane_target(A, gr, bx, lane, p, slot);
     float aol = 0.0f;
-    if (relative && valid) {
-      const double *v = A.a_old + 3ull * (A.perm[p] - bx.p_off);
-      aol = (float)(bx.alpha * sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]));  // against G M
-    }
+    if (relative && valid) aol = alpha_aold(A, bx, p);  // against G M
     int o0 = 0, o1 = 0, o2 = 0;
     float xr = 0.0f, yr = 0.0f, zr = 0.0f;
-    if (valid) {
-      uint32_t cc[3];
-      key_cell(A.skeys[p], bx.curve, cc);
-      o0 = 2 * (int)cc[0] + 1;
-      o1 = 2 * (int)cc[1] + 1;
-      o2 = 2 * (int)cc[2] + 1;
-      const double h22 = bx.L * 0x1p-22;
-      const double4 q = A.part64[p];
-      xr = (float)(q.x - (bx.lo[0] + (double)o0 * h22));
-      yr = (float)(q.y - (bx.lo[1] + (double)o1 * h22));
-      zr = (float)(q.z - (bx.lo[2] + (double)o2 * h22));
-    }
+    if (valid) lane_origin(A, bx, p, A.part64[p], o0, o1, o2, xr, yr, zr);
     // node centre minus lane origin in half-cells, as in the per-target
     // mixed walk: a scalar reduction against the first lane's origin g, and a
     // fixed per-lane term; groups wider than r_cut + |o - g| allows take the
@@ -1821,6 +2212,28 @@ static bool env_flag(const char *name) {
 }
 static bool wide_nodes_forced() { return env_flag("OG_WIDE_NODES"); }
 
+// Up to how many targets the eight-lane walk takes (0: none).  It is faster
+// while the 64-target walks cannot fill the chip, and as long as its vector
+// loads and per-target tests cost less than their idle waves.  Measured
+// against them (clustered and smooth boxes, mixed | FP64, times as fast):
+//   all of     1k     32k    65k    100k   150k   200k   300k   400k targets
+//   clustered  3.8|5.3 1.9|2.6 1.7|2.0 1.4|1.8 1.2|1.7 0.95|1.4 0.84|1.3 0.6|1.0
+//   smooth            2.9|3.4        1.8|1.7        1.05|1.1 0.98|1.06
+//   isolated   (20k) 2.3|4.7, (60k) 1.2|2.2, (100k) 0.8|1.4, (200k) 0.5|0.9
+//   list of 2M        21|27 (1k)  2.7|3.0 (100k) 1.5|1.9 (200k) 1.2|1.6 (300k)
+//                     0.94|1.35 (400k) 0.7|1.0 (600k)
+// so the line lies at 160k (mixed) and 320k (FP64), lower without a cutoff
+// (no node is pruned, so a 64-target wave's lanes mostly agree), and twice as
+// high for lists of a quarter of the particles or less (whose targets lie
+// apart).  OG_EIGHT_MAX=n sets the line (the tests compare both sides); read
+// at each launch.
+static uint32_t eight_lane_max(const WalkArgs &W, int precision) {
+  if (!W.few || W.group_lists || wide_nodes_forced()) return 0;
+  if (const char *e = getenv("OG_EIGHT_MAX")) return (uint32_t)atoi(e);
+  const uint32_t line = W.box_kind == 3 ? (precision == 0 ? 150000u : 70000u) : (precision == 0 ? 320000u : 160000u);
+  return std::max(line, std::min(2 * line, W.n_particles / 4));
+}
+
 void launch_walk(const WalkArgs &W0, int precision, hipStream_t s) {
   const TraceRange trace_range(precision == 0 ? "walk: fp64" : "walk: mixed");
   WalkArgs W = W0;
@@ -1847,6 +2260,23 @@ void launch_walk(const WalkArgs &W0, int precision, hipStream_t s) {
       else k_walkg32<0, false><<<blocks, kWalk32Threads, 0, s>>>(W);
     }
     return;
+  }
+  W.small_max = env_flag("OG_WALK64_PLAIN") && precision == 0 ? 0u : eight_lane_max(W, precision);
+  const uint32_t most = W.n_targets;  // of a list made on the device: a bound
+  if (W.small_max > 0 && (W.dev_count || most <= W.small_max)) {
+    // one wave per workgroup; registers and LDS allow 18 (FP64: 20) per CU
+    const uint32_t waves = W.tkey || W.B == 1 ? (most + kLanes8 - 1) / kLanes8 : groups * ((W.chunk + kLanes8 - 1) / kLanes8);
+    const uint32_t blocks = std::max<uint32_t>(1, std::min<uint32_t>((precision == 0 ? 20u : 18u) * cus, waves));
+    if (precision == 0) {
+      if (W.ext && W.erfc_tail) k_walk8<true, true, true><<<blocks, 64, 0, s>>>(W);
+      else if (W.ext) k_walk8<true, true, false><<<blocks, 64, 0, s>>>(W);
+      else if (W.erfc_tail) k_walk8<true, false, true><<<blocks, 64, 0, s>>>(W);
+      else k_walk8<true, false, false><<<blocks, 64, 0, s>>>(W);
+    } else {
+      if (W.ext) k_walk8<false, true, false><<<blocks, 64, 0, s>>>(W);
+      else k_walk8<false, false, false><<<blocks, 64, 0, s>>>(W);
+    }
+    if (most <= W.small_max) return;
   }
   if (precision == 0 && !W.wide_nodes && !wide_nodes_forced() && !env_flag("OG_WALK64_PLAIN")) {
     // screened FP64 walk: one wave per workgroup, 7 waves per SIMD

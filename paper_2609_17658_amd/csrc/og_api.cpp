@@ -122,6 +122,8 @@ void carve(Carver &c, BuildArrays &A, uint32_t n, uint32_t node_cap, int B, bool
   A.first = c.take<uint32_t>(node_cap);
   A.skip = c.take<uint32_t>(node_cap);
   A.parent = c.take<uint32_t>(node_cap);
+  A.kid = c.take<uint32_t>(node_cap);
+  A.sib = c.take<uint32_t>(node_cap);
   A.top_cap = top_node_bound(node_cap);
   A.top_cnt = c.take<uint32_t>(32);
   A.top_buf = c.take<uint32_t>(kTopWords * A.top_cap);
@@ -310,6 +312,9 @@ WalkArgs Forest::walk_args() const {
   W.part64 = A.part64;
   W.perm = A.perm;
   W.skeys = A.keys_a;
+  W.n_particles = N;
+  W.kid = A.kid;
+  W.sib = A.sib;
   W.chunk = group_max;
   W.list_cap = list_cap;
   W.B = B;
@@ -326,6 +331,9 @@ WalkArgs Forest::walk_args() const {
   W.semin = A.semin;
   if (A.seps) W.ext = 1;
   W.wide_nodes = (uint64_t)node_cap * sizeof(WNode) > 0xffffffffull ? 1 : 0;
+  // 32-bit byte offsets into every array of the walk (so node indices are
+  // below 2^29 too, which kid's packing needs)
+  W.few = !W.wide_nodes && (uint64_t)N * sizeof(double4) <= 0xffffffffull ? 1 : 0;
   // u = r / (2 r_s) < r_cut / (2 r_s) for every pair term (r < r_cut); a margin
   // covers the rounding of u
   for (const auto &b : hboxes)
@@ -339,6 +347,7 @@ int Forest::walk_all(int prec, hipStream_t s, double *acc, double *pot, int pot_
   WalkArgs W = walk_args();
   W.a_old = a_old;
   W.n_groups = n_groups;
+  W.n_targets = N;
   W.acc = acc;
   W.pot = pot;
   W.pot_override = pot_override;

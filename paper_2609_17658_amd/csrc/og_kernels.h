@@ -43,7 +43,8 @@ struct BuildArrays {
   WNode *wnode;
   double4 *cen64;  // per node: FP64 cube centre (x, y, z) and side (w), for the FP64 walks
   uint32_t *first, *skip, *parent;
-  uint32_t *top_cnt;          // [0] top nodes [2] deepest top level
+  uint32_t *kid, *sib;        // per node: its child slots (k_links); the slots
+  uint32_t *top_cnt;          // [0] top nodes [1] child slots taken [2] deepest top level
   uint32_t *top_buf;          // TopArrays' lists, kTopWords per top node (top_cap)
   uint32_t *top_id;           // per node: index of a top node in the top list
   uint32_t top_cap;           // bound on the top nodes (top_node_bound)
@@ -121,10 +122,11 @@ struct WalkArgs {
   const double4 *part64;
   const uint32_t *perm;
   const uint64_t *skeys;      // sorted Morton keys
+  const uint32_t *kid, *sib;  // child slots of the nodes (see k_links)
   uint32_t n_groups;          // walk groups (chunks of `chunk` targets)
   uint32_t chunk;             // targets per group, <= 64
   int list_cap;               // mixed walk list entries per lane (0 = default)
-  uint32_t n_targets;         // length of the target list (tkey != null)
+  uint32_t n_targets;         // targets: length of the list (tkey != null; a bound with dev_count), or all particles
   int B;                      // boxes
   int box_kind;               // shared by all boxes: 1 cutoff+open, 2 cutoff+periodic,
                               // 3 Newtonian+open; 0 mixed
@@ -140,6 +142,9 @@ struct WalkArgs {
   const double *seps, *semax, *semin;  // per-particle softening (null: the boxes' eps)
   int group_lists;            // 1: group-shared interaction lists, 0: per-target walk
   const double *a_old;        // relative criterion: previous accelerations [n][3], caller order
+  uint32_t n_particles;       // particles of the forest
+  uint32_t small_max;         // walks of up to this many targets are eight-lane walks (set by launch_walk)
+  int few;                    // 1: every array within 4 GiB, so the eight-lane walk may run
   int wide_nodes;             // the node records span more than 4 GiB (64-bit record offsets)
   int no_interior;            // mixed walk: reduce every periodic offset (no raw form for interior groups)
   int erfc_tail;              // FP64 walks: some box has r_cut / (2 r_s) >= 3 (library erfc past the polynomial)
