@@ -12,6 +12,8 @@
 // Compiled with -ffp-contract=off: keys and node geometry are rounded
 // exactly as written, which makes them bit-identical to any other IEEE
 // evaluation of the same expressions.
+#include <cstdlib>
+
 #include "og_kernels.h"
 
 namespace og {
@@ -260,13 +262,17 @@ __device__ inline uint32_t cell_of(double x, double lo, double scale, bool &bad)
   return (uint32_t)v;
 }
 
-__global__ __launch_bounds__(kThreads) void k_keys(const BoxDev *boxes, int B, uint32_t n,
-                                                   uint64_t *keys, uint32_t *vals, uint32_t *status) {
-  uint32_t g = blockIdx.x * kThreads + threadIdx.x;
-  if (g >= n) return;
-  const BoxDev &bx = boxes[box_of(boxes, B, g)];
-  uint32_t i = g - bx.p_off;
-  const double *x = bx.pos + 3ull * i;
+// A box's frame, read from its descriptor once.
+struct BoxFrame {
+  double lo[3], scale, box;
+  int periodic, curve;
+  __device__ explicit BoxFrame(const BoxDev &b) : scale(b.scale), box(b.box), periodic(b.periodic), curve(b.curve) {
+    for (int k = 0; k < 3; ++k) lo[k] = b.lo[k];
+  }
+};
+
+// Curve key of a position of a box.
+__device__ inline uint64_t position_key(const BoxFrame &bx, const double x[3], uint32_t *status) {
   bool bad = false;
   uint32_t c[3];
 #pragma unroll
@@ -276,7 +282,15 @@ __global__ __launch_bounds__(kThreads) void k_keys(const BoxDev *boxes, int B, u
     c[k] = cell_of(v, bx.lo[k], bx.scale, bad);
   }
   if (bad) atomicOr(status, kStatusRange);
-  keys[g] = bx.curve ? hilbert3(c[0], c[1], c[2]) : morton3(c[0], c[1], c[2]);
+  return bx.curve ? hilbert3(c[0], c[1], c[2]) : morton3(c[0], c[1], c[2]);
+}
+
+__global__ __launch_bounds__(kThreads) void k_keys(const BoxDev *boxes, int B, uint32_t n,
+                                                   uint64_t *keys, uint32_t *vals, uint32_t *status) {
+  uint32_t g = blockIdx.x * kThreads + threadIdx.x;
+  if (g >= n) return;
+  const BoxDev &bx = boxes[box_of(boxes, B, g)];
+  keys[g] = position_key(BoxFrame(bx), bx.pos + 3ull * (g - bx.p_off), status);
   vals[g] = g;
 }
 
@@ -427,24 +441,246 @@ __global__ __launch_bounds__(kThreads) void k_sort_scatter(const uint64_t *keys_
 }
 
 // -------------------------------------------------------------- gather --
-__global__ __launch_bounds__(kThreads) void k_gather(const BoxDev *boxes, int B, uint32_t n,
-                                                     const uint32_t *vals, uint32_t *perm,
-                                                     uint32_t *inv, double4 *part64, double *seps,
-                                                     uint32_t *status) {
+// A box's caller arrays, read from its descriptor once (in the loops below
+// the compiler would read them again after every store).
+struct BoxIn {
+  const double *pos, *mass, *epsp;
+  double eps;
+  uint32_t p_off;
+  __device__ explicit BoxIn(const BoxDev &b) : pos(b.pos), mass(b.mass), epsp(b.epsp), eps(b.eps), p_off(b.p_off) {}
+};
+
+// What a build's sort leaves for sorted place p of particle g: the FP64
+// particle, the permutation and its inverse, the softening length.
+struct SortedOut {
+  uint32_t *perm, *inv;
+  double4 *part64;
+  double *seps;
+  uint32_t *status;
+  __device__ inline void put(const BoxIn &bx, uint32_t g, uint32_t p) const {
+    const uint32_t i = g - bx.p_off;
+    const double *x = bx.pos + 3ull * i;
+    part64[p] = make_double4(x[0], x[1], x[2], bx.mass[i]);
+    perm[p] = g;
+    inv[g] = p;
+    if (seps) {
+      const double e = bx.epsp ? bx.epsp[i] : bx.eps;
+      if (!(e > 0.0 && e < INFINITY)) atomicOr(status, kStatusRange);
+      seps[p] = e;
+    }
+  }
+};
+
+__global__ __launch_bounds__(kThreads) void k_gather(const BoxDev *boxes, int B, uint32_t n, const uint32_t *vals,
+                                                     SortedOut out) {
   uint32_t p = blockIdx.x * kThreads + threadIdx.x;
   if (p >= n) return;
-  uint32_t g = vals[p];
-  const BoxDev &bx = boxes[box_of(boxes, B, g)];
-  uint32_t i = g - bx.p_off;
-  const double *x = bx.pos + 3ull * i;
-  part64[p] = make_double4(x[0], x[1], x[2], bx.mass[i]);
-  perm[p] = g;
-  inv[g] = p;
-  if (seps) {
-    const double e = bx.epsp ? bx.epsp[i] : bx.eps;
-    if (!(e > 0.0 && e < INFINITY)) atomicOr(status, kStatusRange);
-    seps[p] = e;
+  const uint32_t g = vals[p];
+  out.put(BoxIn(boxes[box_of(boxes, B, g)]), g, p);
+}
+
+// --------------------------------------------------------- merge sort --
+// Sorts of small boxes and short target lists.  The radix sort above takes 24
+// launches of 2.5 to 15 us each whatever the size, since its tiles of 4096
+// keys leave a small sort a few workgroups at a time: 125 us for 1e3 keys,
+// 180-190 us from 3e4 to 3e5.  Here a workgroup sorts a tile of 1024 in LDS
+// (26 us, a chain of some fifty LDS reads), and a launch merges eight runs
+// into one (17-25 us, 11 to 17 dependent reads), so a box takes one launch up
+// to 1024 particles, two up to 8192, three up to 65536.  Both merge by rank: every element finds its place from its own run and from
+// binary searches in the others (after the equal keys of earlier runs, before
+// those of later ones, so the order is stable), which leaves no serial part.
+// The first launch forms the keys and the last one writes the sorted
+// particles, so neither is a pass of its own.  A box's tiles start at its
+// first particle and are merged among themselves, so a batch needs no passes
+// over box numbers.
+constexpr uint32_t kMergeWays = 8;
+constexpr uint32_t kMergePer = kMergeTile / kThreads;  // elements per thread
+
+// What is sorted: boxes' particles by curve key (idx null), or the targets
+// idx[0 .. M) by their particles' places in the tree's order.
+struct MergeIn {
+  const BoxDev *boxes;
+  int B;
+  uint32_t n;           // particles, or targets
+  const int64_t *idx;
+  const uint32_t *inv;
+  uint32_t *status;
+  // segment (box, or the target list) of element g, as [first, first + len)
+  __device__ inline int segment(uint32_t g, uint32_t &first, uint32_t &len) const {
+    if (idx) {
+      first = 0;
+      len = n;
+      return 0;
+    }
+    const int b = B == 1 ? 0 : box_of(boxes, B, g);
+    first = boxes[b].p_off;
+    len = boxes[b].n;
+    return b;
   }
+  // Keys of kMergePer consecutive elements from g, reading none past `last`.
+  __device__ inline void get_keys(int b, uint32_t g, uint32_t last, uint64_t k[kMergePer]) const {
+    if (!idx) {
+      const BoxFrame fr(boxes[b]);
+      const double *pos = boxes[b].pos;
+      const uint32_t off = boxes[b].p_off;
+      double x[kMergePer][3];
+#pragma unroll
+      for (uint32_t q = 0; q < kMergePer; ++q)  // all loads before the first use
+#pragma unroll
+        for (int a = 0; a < 3; ++a) x[q][a] = pos[3ull * (min(g + q, last) - off) + a];
+#pragma unroll
+      for (uint32_t q = 0; q < kMergePer; ++q) k[q] = position_key(fr, x[q], status);
+      return;
+    }
+    int64_t i[kMergePer];
+#pragma unroll
+    for (uint32_t q = 0; q < kMergePer; ++q) i[q] = idx[min(g + q, last)];
+#pragma unroll
+    for (uint32_t q = 0; q < kMergePer; ++q) {
+      if (i[q] < 0 || i[q] >= (int64_t)boxes[0].n) {  // reported through the tree's status word
+        atomicOr(status, kStatusTarget);
+        i[q] = 0;
+      }
+      k[q] = inv[(uint32_t)i[q]];
+    }
+  }
+};
+
+// kLast (of a build): the sorted particles are written too.
+template <bool kLast>
+__global__ __launch_bounds__(kThreads) void k_merge_tiles(MergeIn in, uint64_t *keys, uint32_t *vals, SortedOut out) {
+  __shared__ uint64_t sk[2][kMergeTile];
+  __shared__ uint16_t si[2][kMergeTile];  // place in the tile before the sort
+  // tile blockIdx.x: of the box whose tiles include it
+  int b = 0;
+  uint32_t first = 0, len = in.n, t = blockIdx.x;
+  if (!in.idx) {
+    int hi = in.B - 1;
+    while (b < hi) {
+      const int mid = (b + hi + 1) >> 1;
+      if (in.boxes[mid].t_off <= blockIdx.x) b = mid; else hi = mid - 1;
+    }
+    first = in.boxes[b].p_off;
+    len = in.boxes[b].n;
+    t -= in.boxes[b].t_off;
+  }
+  const uint32_t base = first + t * kMergeTile, cnt = min(kMergeTile, len - t * kMergeTile);
+  {
+    // every thread's elements are neighbours, sorted in registers first (a
+    // place past the tile's end holds the largest key and stays there)
+    uint64_t k[kMergePer];
+    uint32_t v[kMergePer];
+    in.get_keys(b, base + threadIdx.x * kMergePer, base + cnt - 1u, k);
+#pragma unroll
+    for (uint32_t q = 0; q < kMergePer; ++q) {
+      v[q] = threadIdx.x * kMergePer + q;
+      if (v[q] >= cnt) k[q] = ~0ull;
+    }
+    auto order = [&](uint32_t x, uint32_t y) {  // x < y; equal keys keep their order
+      if (k[x] > k[y] || (k[x] == k[y] && v[x] > v[y])) {
+        const uint64_t tk = k[x];
+        const uint32_t tv = v[x];
+        k[x] = k[y];
+        v[x] = v[y];
+        k[y] = tk;
+        v[y] = tv;
+      }
+    };
+    static_assert(kMergePer == 4, "the network below sorts four");
+    order(0, 1);
+    order(2, 3);
+    order(0, 2);
+    order(1, 3);
+    order(1, 2);
+#pragma unroll
+    for (uint32_t q = 0; q < kMergePer; ++q) {
+      sk[0][threadIdx.x * kMergePer + q] = k[q];
+      si[0][threadIdx.x * kMergePer + q] = (uint16_t)v[q];
+    }
+  }
+  lds_barrier();
+  int cur = 0;
+  for (uint32_t r = kMergePer; r < cnt; r <<= 1) {  // runs of r merged in pairs
+    const uint64_t *k0 = sk[cur];
+    uint64_t key[kMergePer], lim[kMergePer];  // elements below lim come first
+    uint32_t pos[kMergePer], oth[kMergePer], len2[kMergePer];
+#pragma unroll
+    for (uint32_t q = 0; q < kMergePer; ++q) {
+      const uint32_t i = threadIdx.x + q * kThreads;
+      const bool right = (i & r) != 0;
+      key[q] = k0[i];
+      lim[q] = key[q] + (right ? 1u : 0u);  // keys are below 2^63
+      oth[q] = (i & ~(2u * r - 1u)) + (right ? 0u : r);
+      len2[q] = i < cnt && oth[q] < cnt ? min(r, cnt - oth[q]) : 0u;
+      pos[q] = 0;
+    }
+    // no branches: the four searches' loads are in flight together
+    for (uint32_t h = r; h; h >>= 1) {
+#pragma unroll
+      for (uint32_t q = 0; q < kMergePer; ++q) {
+        const uint32_t at = pos[q] + h;
+        const uint64_t v = k0[min(oth[q] + at, kMergeTile) - 1u];
+        pos[q] = at <= len2[q] && v < lim[q] ? at : pos[q];
+      }
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kMergePer; ++q) {
+      const uint32_t i = threadIdx.x + q * kThreads;
+      if (i >= cnt) continue;
+      const uint32_t o = (i & ~(2u * r - 1u)) + (i & (r - 1u)) + pos[q];
+      sk[cur ^ 1][o] = key[q];
+      si[cur ^ 1][o] = si[cur][i];
+    }
+    cur ^= 1;
+    lds_barrier();
+  }
+  const BoxIn bx(in.boxes[b]);
+  // places past the end write the last element once more: no branches, so
+  // that the loads of all four are in flight together
+#pragma unroll
+  for (uint32_t q = 0; q < kMergePer; ++q) {
+    const uint32_t i = min(threadIdx.x + q * kThreads, cnt - 1u), g = base + si[cur][i];
+    keys[base + i] = sk[cur][i];
+    vals[base + i] = g;
+    if (kLast) out.put(bx, g, base + i);
+  }
+}
+
+// Sorted runs of `run` elements (a power of two; counted from each segment's
+// first element) merged eight at a time.
+template <bool kLast>
+__global__ __launch_bounds__(kThreads) void k_merge_runs(MergeIn in, uint32_t run, const uint64_t *keys_in,
+                                                         const uint32_t *vals_in, uint64_t *keys_out,
+                                                         uint32_t *vals_out, SortedOut out) {
+  const uint32_t g = blockIdx.x * kThreads + threadIdx.x;
+  if (g >= in.n) return;
+  uint32_t first, len;
+  const int b = in.segment(g, first, len);
+  const uint32_t i = g - first, own = i / run % kMergeWays;
+  const uint32_t gbase = i / (run * kMergeWays) * (run * kMergeWays);
+  const uint64_t key = keys_in[g];
+  const uint64_t *k0 = keys_in + first + gbase;
+  const uint32_t glen = len - gbase;  // elements from the group's start to the segment's end
+  uint32_t pos[kMergeWays];
+#pragma unroll
+  for (uint32_t w = 0; w < kMergeWays; ++w) pos[w] = 0;
+  if (glen > run) {
+    for (uint32_t h = run; h; h >>= 1) {
+#pragma unroll
+      for (uint32_t w = 0; w < kMergeWays; ++w) {
+        const uint32_t at = pos[w] + h, to = w * run + at;
+        const uint64_t v = k0[min(to, glen) - 1u];  // keys are below 2^63
+        pos[w] = w != own && at <= run && to <= glen && v < key + (w < own ? 1u : 0u) ? at : pos[w];
+      }
+    }
+  }
+  uint32_t o = gbase + i % run;
+#pragma unroll
+  for (uint32_t w = 0; w < kMergeWays; ++w) o += pos[w];
+  const uint32_t v = vals_in[g];
+  keys_out[first + o] = key;
+  vals_out[first + o] = v;
+  if (kLast) out.put(BoxIn(in.boxes[b]), v, first + o);
 }
 
 // ------------------------------------------------------------ topology --
@@ -584,12 +820,15 @@ __global__ __launch_bounds__(kThreads) void k_emit(const BoxDev *boxes, int B, u
 // take a node's children side by side where the skip chain gives one after
 // another.  A workgroup reserves the slots of its nodes with one atomic; the
 // order of the reservations shows only in the slot numbers.
-__global__ __launch_bounds__(kThreads) void k_links(const Topo *topo, const uint32_t *skip, const uint32_t *scalars,
-                                                    uint32_t node_cap, uint32_t *parent, uint32_t *kid, uint32_t *sib,
-                                                    uint32_t *slots) {
-  __shared__ uint32_t tmp[kWaves], s_base;
-  const uint32_t tot = min(scalars[3], node_cap);
-  for (uint32_t r0 = blockIdx.x * kThreads; r0 < tot; r0 += gridDim.x * kThreads) {
+// Workgroups of 1024: one atomic per 1024 nodes (the atomics take 11 ns each
+// on their word: with 256 they were 33 of 42 us at 2M particles).
+constexpr int kLinkThreads = 1024;
+__global__ __launch_bounds__(kLinkThreads) void k_links(const Topo *topo, const uint32_t *skip, const uint32_t *scalars,
+                                                        uint32_t node_cap, uint32_t *parent, uint32_t *kid,
+                                                        uint32_t *sib, uint32_t *slots) {
+  __shared__ uint32_t wtot[kLinkThreads / 64], s_base;
+  const uint32_t tot = min(scalars[3], node_cap), lane = lane_id(), w = threadIdx.x >> 6;
+  for (uint32_t r0 = blockIdx.x * kLinkThreads; r0 < tot; r0 += gridDim.x * kLinkThreads) {
     const uint32_t r = r0 + threadIdx.x;
     uint32_t ch[8], k = 0;
     if (r < tot) {
@@ -609,18 +848,31 @@ __global__ __launch_bounds__(kThreads) void k_links(const Topo *topo, const uint
         }
       }
     }
-    uint32_t total;
-    const uint32_t at = block_exscan<true>(k, tmp, &total);
+    uint32_t x = k;  // inclusive scan over the wave, then over the waves
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t u = __shfl_up(x, off, 64);
+      if (lane >= (uint32_t)off) x += u;
+    }
+    if (lane == 63) wtot[w] = x;
+    lds_barrier();
+    uint32_t before = 0, total = 0;
+#pragma unroll
+    for (uint32_t v = 0; v < kLinkThreads / 64; ++v) {
+      const uint32_t u = wtot[v];
+      if (v < w) before += u;
+      total += u;
+    }
     if (threadIdx.x == 0) s_base = total ? atomicAdd(slots, total) : 0u;
     lds_barrier();
-    const uint32_t base = s_base + at;
+    const uint32_t base = s_base + before + x - k;
     if (k && base + k <= node_cap) {
       kid[r] = base << 3 | (k - 1u);
 #pragma unroll
       for (int q = 0; q < 8; ++q)
         if ((uint32_t)q < k) sib[base + q] = ch[q];
     }
-    lds_barrier();  // s_base is read before the next round sets it
+    lds_barrier();  // wtot and s_base are read before the next round sets them
   }
 }
 
@@ -1193,6 +1445,49 @@ bool radix_sort(uint64_t *keys_a, uint32_t *vals_a, uint64_t *keys_b, uint32_t *
   return in_b;
 }
 
+// Whether boxes of up to `longest` particles (n in all), or a list of n
+// targets, take the merge sort.  Measured against the radix sort, build of
+// one box (us, clustered): 1e3 204|102, 3.3e4 282|167, 2.6e5 319|230, 5.1e5
+// 368|309, 1e6 450|511, 2.1e6 662|944: its searches grow with the size and
+// cost more than launches from 6e5 on, and from 1.5e6 in a batch (which saves
+// the passes over box numbers too: 1.4e6 in 32 boxes 4.19|4.09 ms with the
+// walk).  A target list sorts two or three digits only: 10 targets of 2.1e6
+// 368|324 us with the walk, 8192 579|546, 20000 607|594, 1e5 1166|1180.
+// OG_MERGE_MAX=n sets the line (the tests compare both sides).
+bool merge_sorted(uint32_t longest, uint32_t n, bool list) {
+  if (const char *e = std::getenv("OG_MERGE_MAX")) return n <= (uint32_t)std::atoi(e);
+  return list ? n <= 16384u : longest <= 600000u && n <= 1500000u;
+}
+
+// Merge launches of a merge sort whose longest segment has n elements.
+inline int merge_levels(uint32_t n) {
+  int m = 0;
+  for (uint64_t r = kMergeTile; r < n; r *= kMergeWays) ++m;
+  return m;
+}
+
+// Merge sort (see k_merge_tiles) of segments of up to `longest` elements in
+// `tiles` tiles; the result is in keys_a, vals_a.  kBuild: the last launch
+// writes the sorted particles.
+template <bool kBuild>
+void merge_sort(const MergeIn &in, uint32_t longest, uint32_t tiles, uint64_t *keys_a, uint32_t *vals_a,
+                uint64_t *keys_b, uint32_t *vals_b, const SortedOut &out, hipStream_t s) {
+  const int levels = merge_levels(longest);
+  uint64_t *k0 = levels & 1 ? keys_b : keys_a, *k1 = levels & 1 ? keys_a : keys_b;
+  uint32_t *v0 = levels & 1 ? vals_b : vals_a, *v1 = levels & 1 ? vals_a : vals_b;
+  if (kBuild && levels == 0) k_merge_tiles<true><<<tiles, kThreads, 0, s>>>(in, k0, v0, out);
+  else k_merge_tiles<false><<<tiles, kThreads, 0, s>>>(in, k0, v0, out);
+  uint32_t run = kMergeTile;
+  for (int l = 0; l < levels; ++l, run *= kMergeWays) {
+    if (kBuild && l == levels - 1)
+      k_merge_runs<true><<<cdiv(in.n, kThreads), kThreads, 0, s>>>(in, run, k0, v0, k1, v1, out);
+    else
+      k_merge_runs<false><<<cdiv(in.n, kThreads), kThreads, 0, s>>>(in, run, k0, v0, k1, v1, out);
+    std::swap(k0, k1);
+    std::swap(v0, v1);
+  }
+}
+
 void launch_build(BuildArrays &A, hipStream_t s) {
   const uint32_t n = A.n;
   const uint32_t nb = cdiv(n, kThreads);
@@ -1204,25 +1499,32 @@ void launch_build(BuildArrays &A, hipStream_t s) {
     k_frame_reduce<<<cdiv(n, tile), kThreads, 0, s>>>(A.boxes, A.B, n, tile, A.minmax, &A.scalars[0]);
     k_frame_finalize<<<cdiv(A.B, 64), 64, 0, s>>>(A.boxes, A.B, A.minmax);
   }
-  // Start in the buffer pair that makes the sorted result land in *_a.
-  const int box_passes = A.B <= 1 ? 0 : (A.B <= 256 ? 1 : 2);
-  const bool odd = ((8 + box_passes) & 1) != 0;
-  uint64_t *k0 = odd ? A.keys_b : A.keys_a, *k1 = odd ? A.keys_a : A.keys_b;
-  uint32_t *v0 = odd ? A.vals_b : A.vals_a, *v1 = odd ? A.vals_a : A.vals_b;
-  {
-    const TraceRange r("build: keys");
-    k_keys<<<nb, kThreads, 0, s>>>(A.boxes, A.B, n, k0, v0, &A.scalars[0]);
-  }
-  {
-    const TraceRange r("build: radix sort");
-    radix_sort(k0, v0, k1, v1, n, 0, 8, box_passes, A.boxes, A.B, A.hist, A.digit_tot, s);
+  const SortedOut sorted{A.perm, A.inv, A.part64, A.seps, &A.scalars[0]};
+  if (merge_sorted(A.max_n, n, false)) {
+    const TraceRange r("build: merge sort");
+    merge_sort<true>(MergeIn{A.boxes, A.B, n, nullptr, nullptr, &A.scalars[0]}, A.max_n, A.n_tiles, A.keys_a, A.vals_a,
+                     A.keys_b, A.vals_b, sorted, s);
+  } else {
+    // Start in the buffer pair that makes the sorted result land in *_a.
+    const int box_passes = A.B <= 1 ? 0 : (A.B <= 256 ? 1 : 2);
+    const bool odd = ((8 + box_passes) & 1) != 0;
+    uint64_t *k0 = odd ? A.keys_b : A.keys_a, *k1 = odd ? A.keys_a : A.keys_b;
+    uint32_t *v0 = odd ? A.vals_b : A.vals_a, *v1 = odd ? A.vals_a : A.vals_b;
+    {
+      const TraceRange r("build: keys");
+      k_keys<<<nb, kThreads, 0, s>>>(A.boxes, A.B, n, k0, v0, &A.scalars[0]);
+    }
+    {
+      const TraceRange r("build: radix sort");
+      radix_sort(k0, v0, k1, v1, n, 0, 8, box_passes, A.boxes, A.B, A.hist, A.digit_tot, s);
+    }
+    {
+      const TraceRange r("build: gather");
+      k_gather<<<nb, kThreads, 0, s>>>(A.boxes, A.B, n, A.vals_a, sorted);
+    }
   }
   const uint64_t *skeys = A.keys_a;
-  {
-    const TraceRange r("build: gather");
-    k_gather<<<nb, kThreads, 0, s>>>(A.boxes, A.B, n, A.vals_a, A.perm, A.inv, A.part64, A.seps, &A.scalars[0]);
-  }
-  const uint32_t gnodes = std::max<uint32_t>(1, std::min<uint32_t>(cdiv(A.node_cap, kThreads), 8192));
+  const uint32_t glinks = std::max<uint32_t>(1, std::min<uint32_t>(cdiv(A.node_cap, kLinkThreads), 2048));
   {
     const TraceRange r("build: topology");
     k_lcp_depth<<<nb, kThreads, kThreads + 2 * A.leaf_max + 1, s>>>(A.boxes, A.B, n, A.leaf_max, skeys, A.lcp,
@@ -1231,7 +1533,7 @@ void launch_build(BuildArrays &A, hipStream_t s) {
     k_box_nodes<<<cdiv(A.B, 64), 64, 0, s>>>(A.boxes, A.B, A.S, n, A.node_cap, A.scalars, A.parent, A.sib);
     k_emit<<<nb, kThreads, 0, s>>>(A.boxes, A.B, n, skeys, A.lcp, A.depth, A.S, A.node_cap, A.topo,
                                    A.first, A.skip);
-    k_links<<<gnodes, kThreads, 0, s>>>(A.topo, A.skip, A.scalars, A.node_cap, A.parent, A.kid, A.sib, A.top_cnt + 1);
+    k_links<<<glinks, kLinkThreads, 0, s>>>(A.topo, A.skip, A.scalars, A.node_cap, A.parent, A.kid, A.sib, A.top_cnt + 1);
   }
   {
     const TraceRange r("build: moments");
@@ -1291,6 +1593,13 @@ void launch_active(const BuildArrays &A, ActiveArrays &T, uint32_t chunk, hipStr
 
 void launch_targets(const BuildArrays &A, TargetArrays &T, hipStream_t s) {
   const uint32_t M = T.M;
+  if (merge_sorted(M, M, true)) {
+    merge_sort<false>(MergeIn{A.boxes, 1, M, T.idx, A.inv, &A.scalars[0]}, M, cdiv(M, kMergeTile), T.tkey_a, T.tval_a,
+                      T.tkey_b, T.tval_b, SortedOut{}, s);
+    T.tkey = T.tkey_a;
+    T.tval = T.tval_a;
+    return;
+  }
   k_reset<<<1, 1, 0, s>>>(&T.scalars[0]);
   k_targets_map<<<cdiv(M, kThreads), kThreads, 0, s>>>(A.boxes, T.idx, M, A.inv, T.tkey_a, T.tval_a,
                                                       &A.scalars[0]);

@@ -253,9 +253,13 @@ int Forest::init(const std::vector<BoxDev> &boxes, uint64_t node_cap_, hipStream
   hboxes = boxes;
   // walk groups: chunks of group_max consecutive sorted particles per box
   uint64_t gtot = 0;
+  uint32_t tiles = 0, max_n = 0;
   for (auto &b : hboxes) {
     b.g_off = (uint32_t)gtot;
     gtot += (b.n + group_max - 1) / group_max;
+    b.t_off = tiles;
+    tiles += (b.n + kMergeTile - 1) / kMergeTile;
+    max_n = std::max(max_n, b.n);
   }
   n_groups = (uint32_t)gtot;
   bool soft = false;
@@ -281,6 +285,8 @@ int Forest::init(const std::vector<BoxDev> &boxes, uint64_t node_cap_, hipStream
   A.B = B;
   A.n = N;
   A.node_cap = node_cap;
+  A.max_n = max_n;
+  A.n_tiles = tiles;
   A.any_open = 0;
   A.leaf_max = 1;
   for (auto &b : hboxes) {

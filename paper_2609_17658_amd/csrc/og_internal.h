@@ -53,6 +53,7 @@ struct BoxDev {
   uint32_t root, node_end;  // node range, written on the device
   int32_t periodic, cutoff, leaf_max;
   uint32_t g_off;          // first walk group of this box
+  uint32_t t_off;          // first sort tile of this box
   int32_t spline, relative;  // softening kernel, opening criterion
   double hs, alpha;          // spline support 2.8 eps; relative tolerance
   float hsf, hinvf;          // FP32 support and its inverse
@@ -148,6 +149,8 @@ __host__ __device__ inline uint64_t morton3(uint32_t cx, uint32_t cy, uint32_t c
 // is a run of 8^(21-l) consecutive keys whose top 3l bits name the cell.
 __host__ __device__ inline uint64_t hilbert3(uint32_t x, uint32_t y, uint32_t z) {
   uint32_t c[3] = {x, y, z};
+  // (the bit loops stay loops: unrolled, four keys fill the instruction cache)
+#pragma unroll 1
   for (uint32_t q = 1u << (kLevels - 1); q > 1; q >>= 1) {
     const uint32_t low = q - 1;
     for (int i = 0; i < 3; ++i) {
@@ -163,6 +166,7 @@ __host__ __device__ inline uint64_t hilbert3(uint32_t x, uint32_t y, uint32_t z)
   c[1] ^= c[0];
   c[2] ^= c[1];
   uint32_t flip = 0;
+#pragma unroll 1
   for (uint32_t q = 1u << (kLevels - 1); q > 1; q >>= 1)
     if (c[2] & q) flip ^= q - 1;
   return morton3(c[0] ^ flip, c[1] ^ flip, c[2] ^ flip);

@@ -22,11 +22,15 @@ bool radix_sort(uint64_t *keys_a, uint32_t *vals_a, uint64_t *keys_b, uint32_t *
                 int B, uint32_t *hist, uint32_t *digit_tot, hipStream_t s);
 size_t radix_hist_words(uint32_t n);
 
+// Tile of the merge sort that small boxes and target lists take.
+constexpr uint32_t kMergeTile = 1024;
+
 struct BuildArrays {
   BoxDev *boxes;
   int B;
   uint32_t n;                 // total particles
   uint32_t node_cap;          // node capacity
+  uint32_t max_n, n_tiles;    // particles of the largest box; sort tiles of all boxes (kMergeTile each)
   uint64_t *minmax;           // [B][6] ordered-bits min/max for open boxes
   uint64_t *keys_a, *keys_b;
   uint32_t *vals_a, *vals_b;
