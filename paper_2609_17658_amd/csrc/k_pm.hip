@@ -10,7 +10,8 @@
 //   1. deposit: cloud-in-cell weights onto the nodes j*L/n, summed in
 //      64-bit fixed point (a power-of-two scale fitted to N * max m), so
 //      the mesh does not depend on the order of the additions.  Caller
-//      order: atomics onto the mesh.  A tree's curve order: one workgroup
+//      order: atomics onto the mesh, or from 5e5 particles on the blocks of
+//      the tree order after a sort by block.  A tree's curve order: one workgroup
 //      per block of 8^3 cells sums its particles in LDS and stores its
 //      nodes (plus a halo for the blocks above);
 //   2. forward 3-D FFT of the density: length-n transforms along z (the
@@ -26,7 +27,7 @@
 #include <cmath>
 #include <cstdlib>
 
-#include "og_internal.h"
+#include "og_kernels.h"
 #include "og_pm.h"
 
 namespace og {
@@ -51,12 +52,15 @@ __global__ __launch_bounds__(kPmThreads) void k_fill_u64(unsigned long long *p, 
     p[i] = 0ull;
 }
 
-// Particle i: caller arrays, or a tree's particles in curve order.
+// Particle i: caller arrays (in the order ord when given), or a tree's
+// particles in curve order.
 struct PartRef {
   const double *pos, *mass;
   const double4 *part;
+  const uint32_t *ord;
   __device__ inline double4 get(uint32_t i) const {
     if (part) return part[i];
+    if (ord) i = ord[i];
     return make_double4(pos[3ull * i], pos[3ull * i + 1], pos[3ull * i + 2], mass[i]);
   }
 };
@@ -179,8 +183,36 @@ __global__ __launch_bounds__(kPmThreads) void k_block_starts(BlockRef R, uint32_
   bstart[h] = lo;
 }
 
+// Caller-order particles are put in block order first (k_block_keys and the
+// radix sort), the block's number (its x, y, z position row by row) being the
+// key: shift3 = 0, curve kCurveRows.
+constexpr int kCurveRows = -1;
+
+__global__ __launch_bounds__(kPmThreads) void k_block_keys(PartRef P, uint32_t N, int n, double inv_d, uint64_t *keys,
+                                                           uint32_t *vals) {
+  const uint32_t i = blockIdx.x * kPmThreads + threadIdx.x;
+  if (i >= N) return;
+  uint32_t b = 0;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    int c;
+    double f;
+    cic(P.pos[3ull * i + k], n, inv_d, c, f);
+    b = b * (uint32_t)(n / kBlk) + (uint32_t)c / kBlk;
+  }
+  keys[i] = b;
+  vals[i] = i;
+}
+
 // Lower mesh corner (in cells) of block h: the cell of its first key.
 __device__ inline void block_corner(const BlockRef &R, uint32_t h, int logn, int g0[3]) {
+  if (R.curve == kCurveRows) {
+    const int lb = logn - 3, m = (1 << lb) - 1;
+    g0[0] = (int)(h >> (2 * lb)) * kBlk;
+    g0[1] = ((int)(h >> lb) & m) * kBlk;
+    g0[2] = ((int)h & m) * kBlk;
+    return;
+  }
   uint32_t c[3];
   key_cell((uint64_t)h << R.shift3, R.curve, c);
   const int sh = kLevels - logn + 3;
@@ -215,7 +247,10 @@ __device__ inline int halo_index(int tx, int ty, int tz) {
 // in an LDS tile, then its 8^3 own nodes stored to the mesh (every node of
 // the mesh is some block's own node, so the mesh needs no clearing) and
 // its halo to halo[block] (added by k_density_blocks).
-__global__ __launch_bounds__(kPmThreads) void k_deposit_blocks(const double4 *part, BlockRef R, uint32_t N, int n,
+// kRows: caller-order particles in block order (their cell as k_deposit
+// takes it).
+template <bool kRows>
+__global__ __launch_bounds__(kPmThreads) void k_deposit_blocks(PartRef P, BlockRef R, uint32_t N, int n,
                                                                int logn, double inv_d,
                                                                const unsigned long long *mmax,
                                                                unsigned long long *mesh,
@@ -229,10 +264,19 @@ __global__ __launch_bounds__(kPmThreads) void k_deposit_blocks(const double4 *pa
   __syncthreads();
   const double scale = fixed_scale(mmax, N);
   for (uint32_t p = s + threadIdx.x; p < e; p += kPmThreads) {
-    const double4 q = part[p];
+    const double4 q = kRows ? P.get(p) : P.part[p];
     int r[3];
     double f[3];
-    tile_cic(q, R, logn, inv_d, g0, r, f);
+    if (kRows) {
+      const double xs[3] = {q.x, q.y, q.z};
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        cic(xs[k], n, inv_d, r[k], f[k]);
+        r[k] = min(max(r[k] - g0[k], 0), kBlk - 1);
+      }
+    } else {
+      tile_cic(q, R, logn, inv_d, g0, r, f);
+    }
     const double m = q.w * scale;
     const double w[3][2] = {{1.0 - f[0], f[0]}, {1.0 - f[1], f[1]}, {1.0 - f[2], f[2]}};
 #pragma unroll
@@ -1150,6 +1194,38 @@ void launch_fft_pass(double2 *data, const PmTables &Tb, int n, int logn, int sig
 }
 }  // namespace
 
+// Scratch of the caller-order deposit by blocks, carved from B.
+struct BinScratch {
+  uint64_t *keys_a, *keys_b;
+  uint32_t *vals_a, *vals_b, *hist, *digit_tot;
+  // Whether this call takes it: enough particles that eight atomics each cost
+  // more than the sort, and room for it in B.  Measured (whole call, us,
+  // atomics|blocks): clustered particles in random order on 256^3 1143|1030 at
+  // 5e5, 2131|1356 at 2.1e6, on 128^3 465|295 at 4e5, 908|399 at 1e6; grid
+  // order, whose atomics mostly hit one line per wave, on 256^3 1011|979 at
+  // 4.9e5, 1207|1098 at 2.1e6, on 128^3 218|234 at 4e5, 256|262 at 1e6; below
+  // 5e5 the launches cost grid-ordered particles more than the atomics (86|135
+  // at 1.5e5 on 64^3).  OG_PM_BIN_MIN=n sets the line (the tests compare both).
+  bool place(const PmArgs &P, uint64_t cells) {
+    const char *e = getenv("OG_PM_BIN_MIN");
+    if (P.N < (e ? (uint32_t)atoi(e) : 500000u)) return false;
+    char *base = reinterpret_cast<char *>(P.B);
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+      char *p = base + off;
+      off += (bytes + 255) & ~(size_t)255;
+      return p;
+    };
+    keys_a = reinterpret_cast<uint64_t *>(take(8ull * P.N));
+    keys_b = reinterpret_cast<uint64_t *>(take(8ull * P.N));
+    vals_a = reinterpret_cast<uint32_t *>(take(4ull * P.N));
+    vals_b = reinterpret_cast<uint32_t *>(take(4ull * P.N));
+    hist = reinterpret_cast<uint32_t *>(take(4 * radix_hist_words(P.N)));
+    digit_tot = reinterpret_cast<uint32_t *>(take(4 * 256));
+    return off <= cells * sizeof(double2);
+  }
+};
+
 void launch_pm(const PmArgs &P, hipStream_t s) {
   const uint64_t cells = (uint64_t)P.n * P.n * P.n;
   const double d = P.L / P.n, inv_d = P.n / P.L;
@@ -1157,7 +1233,7 @@ void launch_pm(const PmArgs &P, hipStream_t s) {
   while ((1 << logn) < P.n) ++logn;
   // the fixed-point mesh aliases A until the fused x pass writes A
   unsigned long long *fixed = reinterpret_cast<unsigned long long *>(P.A);
-  const PartRef R{P.pos, P.mass, P.part};
+  PartRef R{P.pos, P.mass, P.part, nullptr};
   // Tree order: block workgroups (see k_deposit_blocks); the halo entries
   // live in the second half of A, which the fixed-point mesh leaves free.
   const bool blocks = P.part != nullptr && P.keys != nullptr && P.bstart != nullptr;
@@ -1174,11 +1250,28 @@ void launch_pm(const PmArgs &P, hipStream_t s) {
     unsigned long long *hb = fixed + cells;
     k_block_starts<<<blocks_for(nblocks + 1ull, kPmThreads, 1u << 30), kPmThreads, 0, s>>>(BR, P.N, nblocks,
                                                                                           P.bstart);
-    k_deposit_blocks<<<nblocks, kPmThreads, 0, s>>>(P.part, BR, P.N, P.n, logn, inv_d, P.mmax, fixed, hb);
+    k_deposit_blocks<false><<<nblocks, kPmThreads, 0, s>>>(R, BR, P.N, P.n, logn, inv_d, P.mmax, fixed, hb);
     // what blocks of more than kBlockChunk particles left: atomics onto
     // the stored mesh (the halo stays apart until the density is read)
     k_deposit_tiled<<<blocks_for(P.N, kPmThreads, 1u << 30), kPmThreads, 0, s>>>(R, P.N, P.n, inv_d, P.mmax,
                                                                                  fixed, BR);
+    halo = hb;
+  } else if (BinScratch bin; P.bstart != nullptr && bin.place(P, cells)) {
+    // Caller order by blocks: the particles' numbers sorted by block (scratch
+    // in B, which is free until the z pass), then as above.
+    k_block_keys<<<blocks_for(P.N, kPmThreads, 1u << 30), kPmThreads, 0, s>>>(R, P.N, P.n, inv_d, bin.keys_a,
+                                                                             bin.vals_a);
+    int passes = 1;
+    while (((uint64_t)(nblocks - 1) >> (8 * passes)) != 0) ++passes;
+    const bool in_b = radix_sort(bin.keys_a, bin.vals_a, bin.keys_b, bin.vals_b, P.N, 0, passes, 0, nullptr, 1, bin.hist,
+                                 bin.digit_tot, s);
+    BlockRef RB{in_b ? bin.keys_b : bin.keys_a, P.bstart, 0, kCurveRows, 0.0};
+    PartRef RP = R;
+    RP.ord = in_b ? bin.vals_b : bin.vals_a;
+    unsigned long long *hb = fixed + cells;
+    k_block_starts<<<blocks_for(nblocks + 1ull, kPmThreads, 1u << 30), kPmThreads, 0, s>>>(RB, P.N, nblocks, P.bstart);
+    k_deposit_blocks<true><<<nblocks, kPmThreads, 0, s>>>(RP, RB, P.N, P.n, logn, inv_d, P.mmax, fixed, hb);
+    k_deposit_tiled<<<blocks_for(P.N, kPmThreads, 1u << 30), kPmThreads, 0, s>>>(RP, P.N, P.n, inv_d, P.mmax, fixed, RB);
     halo = hb;
   } else {
     // Caller order: direct atomics (neighbouring threads rarely share a node).

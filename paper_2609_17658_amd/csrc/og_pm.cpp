@@ -92,6 +92,7 @@ int og_pm_force(og_pm *pm, const double *pos, const double *mass, int64_t N, dou
   P.B = pm->B;
   P.mmax = pm->mmax;
   P.tables = pm->tables;
+  P.bstart = pm->bstart;
   P.acc = acc;
   P.pot = pot;
   P.accumulate = accumulate ? 1 : 0;

@@ -20,9 +20,9 @@ struct PmArgs {
   double *acc;         // [N][3]
   double *pot;         // [N] or null
   int accumulate;      // 1: add to acc/pot
-  // With part (a periodic tree whose root cube is the mesh box): the tree's
-  // sorted keys and curve, its level-21 cell scale 2^21 / L, and room for
-  // (n/8)^3 + 1 block starts (pm_block_words).
+  // Room for (n/8)^3 + 1 block starts (pm_block_words); with part (a periodic
+  // tree whose root cube is the mesh box) the tree's sorted keys and curve and
+  // its level-21 cell scale 2^21 / L.
   const uint64_t *keys;
   int curve;
   double tscale;
