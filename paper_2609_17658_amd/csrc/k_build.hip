@@ -693,6 +693,27 @@ __global__ __launch_bounds__(kThreads) void k_merge_runs(MergeIn in, uint32_t ru
 // running minima of lcp to the right and to the left (merged, both
 // sequences are non-increasing).  nstart(p) = nodes whose first particle
 // is p = levels lcp(p)+1 .. depth(p).
+// at(j): lcp(p + j).
+template <class At>
+__device__ inline int leaf_depth(uint32_t p, int lm, const At &at) {
+  int ri = 1, li = 1;
+  int rv = at(1);
+  int lv = at(0);
+  int v = -1;
+  for (int k = 0; k < lm; ++k) {
+    if (rv >= lv) {
+      v = rv;
+      ++ri;
+      rv = ri <= lm ? min(rv, at(ri)) : -2;
+    } else {
+      v = lv;
+      ++li;
+      lv = (li <= lm && p + 1 >= (uint32_t)li) ? min(lv, at(1 - li)) : -2;
+    }
+  }
+  return min(kLevels, v + 1);
+}
+
 // The block's lcp values, with a halo of lmax on each side, are formed once
 // in LDS from the keys: lcp(q) = shared levels of keys q-1 and q, -1 at the
 // first particle of a box and outside [0, n).  A particle's running minima
@@ -717,23 +738,7 @@ __global__ __launch_bounds__(kThreads) void k_lcp_depth(const BoxDev *boxes, int
   if (p >= n) return;
   const int lm = boxes[box_of(boxes, B, p)].leaf_max;
   const int8_t *L = sl + (p - lo);  // L[j] = lcp(p + j)
-  const int own = L[0];
-  int ri = 1, li = 1;
-  int rv = L[1];
-  int lv = own;
-  int v = -1;
-  for (int k = 0; k < lm; ++k) {
-    if (rv >= lv) {
-      v = rv;
-      ++ri;
-      rv = ri <= lm ? min(rv, (int)L[ri]) : -2;
-    } else {
-      v = lv;
-      ++li;
-      lv = (li <= lm && p + 1 >= (uint32_t)li) ? min(lv, (int)L[1 - li]) : -2;
-    }
-  }
-  int d = min(kLevels, v + 1);
+  const int own = L[0], d = leaf_depth(p, lm, [&](int j) { return (int)L[j]; });
   lcp[p] = (int8_t)own;
   depth[p] = (uint8_t)d;
   nstart[p] = (uint32_t)max(0, d - own);
@@ -761,7 +766,8 @@ __global__ void k_box_nodes(BoxDev *boxes, int B, const uint32_t *S, uint32_t n,
 
 // End (exclusive) of the level-L node that starts at p: first q in (p, b1]
 // whose key leaves the node's prefix; exponential then binary search.
-__device__ inline uint32_t node_end(const uint64_t *skeys, uint32_t p, int L, uint32_t b1) {
+template <class Keys>
+__device__ inline uint32_t node_end(const Keys &skeys, uint32_t p, int L, uint32_t b1) {
   if (L == 0) return b1;
   const int sh = 63 - 3 * L;
   const uint64_t pre = skeys[p] >> sh;
@@ -780,6 +786,19 @@ __device__ inline uint32_t node_end(const uint64_t *skeys, uint32_t p, int L, ui
   return hi;
 }
 
+// Topology record of the level-L node that holds particles [p, e) around the
+// cell cc, with skip sk.
+__device__ inline Topo node_topo(const uint32_t cc[3], uint32_t p, uint32_t e, int L, bool leaf, uint32_t sk) {
+  const int drop = kLevels - L;
+  const uint64_t corner = (uint64_t)((cc[0] >> drop) << drop) | ((uint64_t)((cc[1] >> drop) << drop) << 21) |
+                          ((uint64_t)((cc[2] >> drop) << drop) << 42);
+  Topo t;
+  t.corner = corner | (leaf ? kLeafBit : 0ull);
+  t.a = leaf ? p : sk;
+  t.b = ((e - p) & kCountMask) | ((uint32_t)L << kCountBits);
+  return t;
+}
+
 __global__ __launch_bounds__(kThreads) void k_emit(const BoxDev *boxes, int B, uint32_t n,
                                                    const uint64_t *skeys, const int8_t *lcp,
                                                    const uint8_t *depth, const uint32_t *S,
@@ -794,20 +813,12 @@ __global__ __launch_bounds__(kThreads) void k_emit(const BoxDev *boxes, int B, u
   const uint64_t key = skeys[p];
   uint32_t cc[3];
   key_cell(key, bx.curve, cc);
-  const uint32_t cx = cc[0], cy = cc[1], cz = cc[2];
   uint32_t rank = S[p];
   for (int L = l0 + 1; L <= d; ++L, ++rank) {
     if (rank >= node_cap) return;
     const uint32_t e = node_end(skeys, p, L, b1);
-    const int drop = kLevels - L;
-    const uint64_t corner = (uint64_t)((cx >> drop) << drop) | ((uint64_t)((cy >> drop) << drop) << 21) |
-                            ((uint64_t)((cz >> drop) << drop) << 42);
-    const bool leaf = (L == d);
     const uint32_t sk = S[e];
-    Topo t;
-    t.corner = corner | (leaf ? kLeafBit : 0ull);
-    t.a = leaf ? p : sk;
-    t.b = ((e - p) & kCountMask) | ((uint32_t)L << kCountBits);
+    const Topo t = node_topo(cc, p, e, L, L == d, sk);
     topo[rank] = t;
     first[rank] = p;
     skip[rank] = sk;
@@ -918,16 +929,23 @@ __device__ inline void walk_records(const BoxDev &bx, const Topo &t, const Mom32
                           ldexp(bx.L, -lev));
 }
 
+// Node r's moments m (cube centre c): FP64 and FP32 forms, then the walk
+// records.
+__device__ inline void node_records(const BoxDev &bx, const Topo &t, uint32_t r, const double c[3], const Mom64 &m,
+                                    Mom64 *mom64, Mom32 *mom32, WNode *wn, double4 *cen64) {
+  mom64[r] = m;
+  const Mom32 m32{(float)(m.cx - c[0]), (float)(m.cy - c[1]), (float)(m.cz - c[2]), (float)m.m};
+  mom32[r] = m32;
+  walk_records(bx, t, m32, r, wn, cen64);
+}
+
 // Mass and centre of mass of node r from its mass M and first moments s
-// about the cube centre c; FP64 and FP32 forms, then the walk records.
+// about the cube centre c, and its records.
 __device__ inline Mom64 store_node(const BoxDev &bx, const Topo &t, uint32_t r, const double c[3], double M,
                                    double s0, double s1, double s2, Mom64 *mom64, Mom32 *mom32, WNode *wn,
                                    double4 *cen64) {
   const Mom64 m{c[0] + s0 / M, c[1] + s1 / M, c[2] + s2 / M, M};
-  mom64[r] = m;
-  const Mom32 m32{(float)(m.cx - c[0]), (float)(m.cy - c[1]), (float)(m.cz - c[2]), (float)M};
-  mom32[r] = m32;
-  walk_records(bx, t, m32, r, wn, cen64);
+  node_records(bx, t, r, c, m, mom64, mom32, wn, cen64);
   return m;
 }
 
@@ -1344,6 +1362,273 @@ __global__ __launch_bounds__(kTopThreads) void k_moments_top(const BoxDev *boxes
   }
 }
 
+// ------------------------------------------------------- small trees --
+// The whole build of one box of up to kSmallN particles and kSmallNodes nodes
+// (by the node bound) in one workgroup: keys, sort, gather, topology, child
+// slots and moments, with the expressions of the kernels above, so the tree is
+// the same to the bit.  Those take 12 launches of 1.5 to 26 us, each waiting
+// for its own chain of memory reads, for work that is a few reads per thread:
+// here the keys, the scan and the moments stay in LDS between the steps (the
+// chain of dependent LDS reads, some 12 us each for the sort and the levels,
+// bounds it).  1000 particles: kernels of the build 92 -> 43 us, build and
+// force 195 -> 132 us.
+constexpr uint32_t kSmallN = 2048, kSmallNodes = 4096;
+constexpr int kSmallThreads = 1024;
+constexpr uint32_t kSmallPer = kSmallN / kSmallThreads, kSmallNodePer = kSmallNodes / kSmallThreads;
+
+// Exclusive scan of one value per thread over kSmallThreads threads.
+__device__ inline uint32_t small_exscan(uint32_t v, uint32_t *wtot, uint32_t *total) {
+  const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
+  uint32_t x = v;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t t = __shfl_up(x, off, 64);
+    if (lane >= (uint32_t)off) x += t;
+  }
+  if (lane == 63) wtot[w] = x;
+  lds_barrier();
+  uint32_t before = 0, tot = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < kSmallThreads / 64; ++i) {
+    const uint32_t t = wtot[i];
+    if (i < w) before += t;
+    tot += t;
+  }
+  lds_barrier();
+  *total = tot;
+  return before + x - v;
+}
+
+struct SmallSort {  // LDS of the steps before the moments
+  uint64_t key[2][kSmallN];
+  uint16_t idx[2][kSmallN];
+  uint32_t S[kSmallN + 1];
+  int8_t lcp[kSmallN];
+};
+
+// init: the status word and counts have not been set by a kernel before.
+__global__ __launch_bounds__(kSmallThreads) void k_build_small(BuildArrays A, SortedOut out, int init) {
+  __shared__ union {
+    SmallSort so;
+    Mom64 mom[kSmallNodes];
+  } u;
+  __shared__ uint16_t send[kSmallNodes];  // per node: the node after its subtree
+  __shared__ uint16_t kid16[kSmallNodes];  // the child slots
+  __shared__ uint32_t wtot[kSmallThreads / 64], s_hi;
+  const uint32_t tid = threadIdx.x, n = A.n;
+  if (tid == 0) {
+    if (init) A.scalars[0] = 0u;
+    A.scalars[4] = n;
+    s_hi = 0;
+  }
+  __syncthreads();  // the status word is clear before a key may mark it
+  // keys, sorted in pairs in registers, then runs merged by rank (as in
+  // k_merge_tiles)
+  {
+    const BoxFrame fr(A.boxes[0]);
+    const double *pos = A.boxes[0].pos;
+    uint64_t k[kSmallPer];
+    double x[kSmallPer][3];
+#pragma unroll
+    for (uint32_t q = 0; q < kSmallPer; ++q)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) x[q][a] = pos[3ull * min(tid * kSmallPer + q, n - 1u) + a];
+#pragma unroll
+    for (uint32_t q = 0; q < kSmallPer; ++q) {
+      k[q] = position_key(fr, x[q], out.status);
+      if (tid * kSmallPer + q >= n) k[q] = ~0ull;
+    }
+    static_assert(kSmallPer == 2, "pairs");
+    const bool swap = k[0] > k[1];
+    u.so.key[0][2 * tid] = swap ? k[1] : k[0];
+    u.so.key[0][2 * tid + 1] = swap ? k[0] : k[1];
+    u.so.idx[0][2 * tid] = (uint16_t)(2 * tid + (swap ? 1u : 0u));
+    u.so.idx[0][2 * tid + 1] = (uint16_t)(2 * tid + (swap ? 0u : 1u));
+  }
+  lds_barrier();
+  int cur = 0;
+  for (uint32_t r = kSmallPer; r < n; r <<= 1) {
+    const uint64_t *k0 = u.so.key[cur];
+    uint64_t key[kSmallPer], lim[kSmallPer];
+    uint32_t at0[kSmallPer], oth[kSmallPer], len2[kSmallPer];
+#pragma unroll
+    for (uint32_t q = 0; q < kSmallPer; ++q) {
+      const uint32_t i = tid + q * kSmallThreads;
+      const bool right = (i & r) != 0;
+      key[q] = k0[i];
+      lim[q] = key[q] + (right ? 1u : 0u);  // keys are below 2^63
+      oth[q] = (i & ~(2u * r - 1u)) + (right ? 0u : r);
+      len2[q] = i < n && oth[q] < n ? min(r, n - oth[q]) : 0u;
+      at0[q] = 0;
+    }
+    for (uint32_t h = r; h; h >>= 1) {
+#pragma unroll
+      for (uint32_t q = 0; q < kSmallPer; ++q) {
+        const uint32_t at = at0[q] + h;
+        const uint64_t v = k0[min(oth[q] + at, kSmallN) - 1u];
+        at0[q] = at <= len2[q] && v < lim[q] ? at : at0[q];
+      }
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kSmallPer; ++q) {
+      const uint32_t i = tid + q * kSmallThreads;
+      if (i >= n) continue;
+      const uint32_t o = (i & ~(2u * r - 1u)) + (i & (r - 1u)) + at0[q];
+      u.so.key[cur ^ 1][o] = key[q];
+      u.so.idx[cur ^ 1][o] = u.so.idx[cur][i];
+    }
+    cur ^= 1;
+    lds_barrier();
+  }
+  const uint64_t *keys = u.so.key[cur];
+  // sorted particles; common levels of neighbours
+  {
+    const BoxIn bx(A.boxes[0]);
+#pragma unroll
+    for (uint32_t q = 0; q < kSmallPer; ++q) {
+      const uint32_t p = tid + q * kSmallThreads;
+      if (p >= n) continue;
+      A.keys_a[p] = keys[p];
+      out.put(bx, u.so.idx[cur][p], p);
+      u.so.lcp[p] = (int8_t)(p ? shared_levels(keys[p - 1], keys[p]) : -1);
+    }
+  }
+  lds_barrier();
+  // depth of every particle's leaf and the nodes that start at it; their ranks
+  const int lm = A.boxes[0].leaf_max, curve = A.boxes[0].curve;
+  uint32_t starts[kSmallPer], mine = 0;
+#pragma unroll
+  for (uint32_t q = 0; q < kSmallPer; ++q) {
+    const uint32_t p = tid * kSmallPer + q;
+    starts[q] = 0;
+    if (p >= n) continue;
+    const int d = leaf_depth(p, lm, [&](int j) {
+      const int64_t x = (int64_t)p + j;
+      return x >= 0 && x < (int64_t)n ? (int)u.so.lcp[x] : -1;
+    });
+    starts[q] = (uint32_t)max(0, d - (int)u.so.lcp[p]);
+    mine += starts[q];
+  }
+  uint32_t tot;
+  uint32_t rank = small_exscan(mine, wtot, &tot);
+#pragma unroll
+  for (uint32_t q = 0; q < kSmallPer; ++q) {
+    const uint32_t p = tid * kSmallPer + q;
+    if (p < n) u.so.S[p] = rank;
+    rank += starts[q];
+  }
+  if (tid == 0) {
+    u.so.S[n] = tot;
+    const uint32_t end = min(tot, A.node_cap);
+    A.boxes[0].root = 0;
+    A.boxes[0].node_end = end;
+    A.scalars[3] = end;
+    if (tot > A.node_cap) atomicOr(&A.scalars[0], kStatusNodes);
+    A.parent[0] = 0xffffffffu;
+    A.sib[0] = 0;
+  }
+  lds_barrier();
+  tot = min(tot, A.node_cap);  // at most kSmallNodes (the launch rule)
+  // a thread per node: the particle it starts at, from the ranks; its level,
+  // from its place among that particle's nodes
+  Topo t[kSmallNodePer];
+#pragma unroll
+  for (uint32_t k = 0; k < kSmallNodePer; ++k) {
+    const uint32_t r = tid + k * kSmallThreads;
+    if (r >= tot) continue;
+    uint32_t p = 0;  // the last particle of rank r or below
+    for (uint32_t h = kSmallN / 2; h; h >>= 1)
+      if (p + h < n && u.so.S[p + h] <= r) p += h;
+    const int L = u.so.lcp[p] + 1 + (int)(r - u.so.S[p]);
+    const bool leaf = r + 1 == u.so.S[p + 1];
+    uint32_t cc[3];
+    key_cell(keys[p], curve, cc);
+    const uint32_t e = node_end(keys, p, L, n), sk = u.so.S[e];
+    t[k] = node_topo(cc, p, e, L, leaf, sk);
+    A.topo[r] = t[k];
+    A.first[r] = p;
+    A.skip[r] = sk;
+    send[r] = (uint16_t)min(leaf ? r + 1 : max(r + 1, sk), tot);
+    atomicMax(&s_hi, (uint32_t)L);
+  }
+  __syncthreads();  // (the sorted particles are read below)
+  // parents and child slots (the root holds slot 0)
+  uint32_t want = 0, kids[kSmallNodePer];
+#pragma unroll
+  for (uint32_t k = 0; k < kSmallNodePer; ++k) {
+    const uint32_t r = tid + k * kSmallThreads;
+    kids[k] = 0;
+    if (r >= tot) continue;
+    if (t[k].corner & kLeafBit) continue;
+    const uint32_t end = send[r];
+    for (uint32_t c = r + 1; c < end && kids[k] < 8; c = send[c]) {
+      A.parent[c] = r;
+      ++kids[k];
+    }
+    want += kids[k];
+  }
+  uint32_t total, first_kid[kSmallNodePer];
+  uint32_t slot = 1u + small_exscan(want, wtot, &total);
+#pragma unroll
+  for (uint32_t k = 0; k < kSmallNodePer; ++k) {
+    const uint32_t r = tid + k * kSmallThreads;
+    first_kid[k] = slot;
+    if (!kids[k]) continue;
+    A.kid[r] = slot << 3 | (kids[k] - 1u);
+    uint32_t c = r + 1;
+    for (uint32_t q = 0; q < kids[k]; ++q, c = send[c]) {
+      A.sib[slot] = c;
+      kid16[slot++] = (uint16_t)c;  // at most tot - 1 slots after the root's
+    }
+  }
+  // Moments in LDS, leaves first, then level by level; the records after all
+  // of them, so that a level costs its sums and divisions only.  (The scan's
+  // barriers lie between the last use of the keys and the first of the
+  // moments, which share their LDS.)
+  const BoxDev &bx = A.boxes[0];
+#pragma unroll
+  for (uint32_t k = 0; k < kSmallNodePer; ++k) {
+    const uint32_t r = tid + k * kSmallThreads;
+    if (r >= tot || !(t[k].corner & kLeafBit)) continue;
+    const uint32_t f = t[k].a, cnt = t[k].b & kCountMask;
+    double c[3];
+    node_centre(bx, t[k].corner, (int)(t[k].b >> kCountBits), c);
+    double M = 0.0, s0 = 0.0, s1 = 0.0, s2 = 0.0;
+    for (uint32_t j = 0; j < cnt; j += 4) {
+      double4 q[4];  // four loads in flight
+#pragma unroll
+      for (uint32_t i = 0; i < 4; ++i) q[i] = A.part64[f + min(j + i, cnt - 1u)];
+#pragma unroll
+      for (uint32_t i = 0; i < 4; ++i)
+        if (j + i < cnt) leaf_add(q[i], c, M, s0, s1, s2);
+    }
+    u.mom[r] = Mom64{c[0] + s0 / M, c[1] + s1 / M, c[2] + s2 / M, M};
+  }
+  for (int L = (int)s_hi; L >= 0; --L) {
+    lds_barrier();  // deeper levels summed
+#pragma unroll
+    for (uint32_t k = 0; k < kSmallNodePer; ++k) {
+      const uint32_t r = tid + k * kSmallThreads;
+      if (!kids[k] || (int)(t[k].b >> kCountBits) != L) continue;
+      ChildSums cs;
+      node_centre(bx, t[k].corner, L, cs.c);
+      for (uint32_t q = 0; q < kids[k]; ++q) cs.add(u.mom[kid16[first_kid[k] + q]]);
+      u.mom[r] = top_mom(cs);
+    }
+  }
+#pragma unroll 1
+  for (uint32_t r = tid; r < tot; r += kSmallThreads) {
+    const Topo tr = A.topo[r];
+    const Mom64 m = u.mom[r];
+    double c[3];
+    node_centre(bx, tr.corner, (int)(tr.b >> kCountBits), c);
+    node_records(bx, tr, r, c, m, A.mom64, A.mom32, A.wnode, A.cen64);
+    if (!(tr.corner & kLeafBit)) continue;
+    const uint32_t f = tr.a, cnt = tr.b & kCountMask;
+    for (uint32_t j = f; j < f + cnt; ++j) A.part32[j] = leaf_offset(A.part64[j], m, bx.Gf);
+  }
+}
+
 // --------------------------------------------------- targets (subsets) --
 __global__ __launch_bounds__(kThreads) void k_targets_map(const BoxDev *boxes, const int64_t *idx,
                                                           uint32_t M, const uint32_t *inv,
@@ -1445,6 +1730,12 @@ bool radix_sort(uint64_t *keys_a, uint32_t *vals_a, uint64_t *keys_b, uint32_t *
   return in_b;
 }
 
+// An environment switch that is set to 1 (the tests compare both sides).
+static bool env_set(const char *name) {
+  const char *e = std::getenv(name);
+  return e && std::atoi(e) == 1;
+}
+
 // Whether boxes of up to `longest` particles (n in all), or a list of n
 // targets, take the merge sort.  Measured against the radix sort, build of
 // one box (us, clustered): 1e3 204|102, 3.3e4 282|167, 2.6e5 319|230, 5.1e5
@@ -1491,7 +1782,11 @@ void merge_sort(const MergeIn &in, uint32_t longest, uint32_t tiles, uint64_t *k
 void launch_build(BuildArrays &A, hipStream_t s) {
   const uint32_t n = A.n;
   const uint32_t nb = cdiv(n, kThreads);
-  k_init_scalars<<<1, 64, 0, s>>>(A.scalars, n, A.top_cnt, A.B);
+  const SortedOut sorted{A.perm, A.inv, A.part64, A.seps, &A.scalars[0]};
+  // one box whose nodes fit one workgroup's LDS (1232 particles with leaves of
+  // up to 8); per-particle lengths take the general path
+  const bool small = A.B == 1 && !A.seps && n <= kSmallN && A.node_cap <= kSmallNodes && !env_set("OG_NO_SMALL_BUILD");
+  if (!small || A.any_open) k_init_scalars<<<1, 64, 0, s>>>(A.scalars, n, A.top_cnt, A.B);
   if (A.any_open) {
     k_frame_init<<<cdiv(6 * (uint64_t)A.B, kThreads), kThreads, 0, s>>>(A.B, A.minmax);
     // at most 256 workgroups: 1536 atomics on one box's six words
@@ -1499,7 +1794,11 @@ void launch_build(BuildArrays &A, hipStream_t s) {
     k_frame_reduce<<<cdiv(n, tile), kThreads, 0, s>>>(A.boxes, A.B, n, tile, A.minmax, &A.scalars[0]);
     k_frame_finalize<<<cdiv(A.B, 64), 64, 0, s>>>(A.boxes, A.B, A.minmax);
   }
-  const SortedOut sorted{A.perm, A.inv, A.part64, A.seps, &A.scalars[0]};
+  if (small) {
+    const TraceRange r("build: one workgroup");
+    k_build_small<<<1, kSmallThreads, 0, s>>>(A, sorted, A.any_open ? 0 : 1);
+    return;
+  }
   if (merge_sorted(A.max_n, n, false)) {
     const TraceRange r("build: merge sort");
     merge_sort<true>(MergeIn{A.boxes, A.B, n, nullptr, nullptr, &A.scalars[0]}, A.max_n, A.n_tiles, A.keys_a, A.vals_a,
