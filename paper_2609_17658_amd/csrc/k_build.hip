@@ -60,76 +60,61 @@ __device__ inline uint32_t block_exscan(uint32_t v, uint32_t *tmp4, uint32_t *to
 }
 
 // ---------------------------------------------------------------- scan --
-__global__ __launch_bounds__(kThreads) void k_scan_reduce(const uint32_t *in, const uint32_t *n_dev,
-                                                          uint32_t *partial) {
-  __shared__ uint32_t tmp[kWaves];
-  const uint32_t n = *n_dev;
-  const uint32_t base = blockIdx.x * kScanTile;
-  if (base >= n) return;
-  uint32_t s = 0;
-  for (uint32_t i = threadIdx.x; i < kScanTile; i += kThreads) {
-    uint32_t e = base + i;
-    if (e < n) s += in[e];
-  }
-  uint32_t tot;
-  block_exscan(s, tmp, &tot);
-  if (threadIdx.x == 0) partial[blockIdx.x] = tot;
+// Sum of partial[0 .. count): all threads get it.
+__device__ inline uint32_t sum_partials(const uint32_t *partial, uint32_t count, uint32_t *tmp4) {
+  uint32_t v = 0, tot;
+  for (uint32_t i = threadIdx.x; i < count; i += kThreads) v += partial[i];
+  block_exscan(v, tmp4, &tot);
+  return tot;
 }
 
-__global__ __launch_bounds__(kThreads) void k_scan_partials(uint32_t *partial, const uint32_t *n_dev) {
-  __shared__ uint32_t tmp[kWaves];
-  const uint32_t n = *n_dev;
-  const uint32_t nb = (n + kScanTile - 1) / kScanTile;
-  uint32_t carry = 0;
-  for (uint32_t base = 0; base < nb; base += kThreads) {
-    uint32_t e = base + threadIdx.x;
-    uint32_t v = e < nb ? partial[e] : 0u;
+// Exclusive scan of n values, tiles of kScanTile, the tiles' sums in `partial`:
+// get(e) is value e, put(e, o) takes its offset o.  A workgroup adds up the sums
+// of the tiles before its run of tiles (from L2; at most kScanGrid runs) instead
+// of waiting for a launch that scans them.  Returns the offset after the run:
+// in the last workgroup, the total.
+constexpr uint32_t kScanGrid = 2048;
+
+template <class Get, class Put>
+__device__ inline uint32_t scan_tiles(uint32_t n, const uint32_t *partial, uint32_t *buf, uint32_t *tmp4, const Get &get,
+                                      const Put &put) {
+  const uint32_t tiles = (n + kScanTile - 1) / kScanTile;
+  const uint32_t t0 = (uint32_t)((uint64_t)tiles * blockIdx.x / gridDim.x);
+  const uint32_t t1 = (uint32_t)((uint64_t)tiles * (blockIdx.x + 1) / gridDim.x);
+  uint32_t before = sum_partials(partial, t0, tmp4);
+  for (uint32_t t = t0; t < t1; ++t) {
+    const uint32_t base = t * kScanTile;
+    if (t > t0) __syncthreads();  // the tile before has been put
+#pragma unroll
+    for (uint32_t k = 0; k < kScanTile / kThreads; ++k) {
+      const uint32_t i = threadIdx.x + k * kThreads, e = base + i;
+      buf[i] = e < n ? get(e) : 0u;
+    }
+    __syncthreads();
+    constexpr uint32_t per = kScanTile / kThreads;  // 16 consecutive values per thread
+    uint32_t loc[per];
+    uint32_t s = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < per; ++k) {
+      loc[k] = buf[threadIdx.x * per + k];
+      s += loc[k];
+    }
     uint32_t tot;
-    uint32_t ex = block_exscan(v, tmp, &tot);
-    if (e < nb) partial[e] = carry + ex;
-    carry += tot;
-  }
-  if (threadIdx.x == 0) partial[nb] = carry;  // grand total
-}
-
-__global__ __launch_bounds__(kThreads) void k_scan_down(const uint32_t *in, uint32_t *out,
-                                                        const uint32_t *n_dev, const uint32_t *partial) {
-  __shared__ uint32_t buf[kScanTile];
-  __shared__ uint32_t tmp[kWaves];
-  const uint32_t n = *n_dev;
-  const uint32_t base = blockIdx.x * kScanTile;
-  const uint32_t nb = (n + kScanTile - 1) / kScanTile;
-  if (base > n) return;
-  if (base == n) {  // n is a multiple of the tile: this block only writes the total
-    if (threadIdx.x == 0) out[n] = partial[nb];
-    return;
-  }
-  for (uint32_t i = threadIdx.x; i < kScanTile; i += kThreads) {
-    uint32_t e = base + i;
-    buf[i] = e < n ? in[e] : 0u;
-  }
-  __syncthreads();
-  constexpr uint32_t per = kScanTile / kThreads;  // 16 consecutive values per thread
-  uint32_t loc[per];
-  uint32_t s = 0;
+    uint32_t ex = block_exscan(s, tmp4, &tot) + before;
 #pragma unroll
-  for (uint32_t k = 0; k < per; ++k) {
-    loc[k] = buf[threadIdx.x * per + k];
-    s += loc[k];
-  }
-  uint32_t tot;
-  uint32_t ex = block_exscan(s, tmp, &tot) + partial[blockIdx.x];
+    for (uint32_t k = 0; k < per; ++k) {
+      buf[threadIdx.x * per + k] = ex;
+      ex += loc[k];
+    }
+    __syncthreads();
 #pragma unroll
-  for (uint32_t k = 0; k < per; ++k) {
-    buf[threadIdx.x * per + k] = ex;
-    ex += loc[k];
+    for (uint32_t k = 0; k < per; ++k) {
+      const uint32_t i = threadIdx.x + k * kThreads, e = base + i;
+      if (e < n) put(e, buf[i]);
+    }
+    before += tot;
   }
-  __syncthreads();
-  for (uint32_t i = threadIdx.x; i < kScanTile; i += kThreads) {
-    uint32_t e = base + i;
-    if (e < n) out[e] = buf[i];
-  }
-  if (blockIdx.x == nb - 1 && threadIdx.x == 0) out[n] = partial[nb];
+  return before;
 }
 
 // --------------------------------------------------------------- frame --
@@ -722,7 +707,8 @@ __device__ inline int leaf_depth(uint32_t p, int lm, const At &at) {
 // contribute min(-1, .) = -1, as when each is evaluated against the box.
 __global__ __launch_bounds__(kThreads) void k_lcp_depth(const BoxDev *boxes, int B, uint32_t n, int lmax,
                                                         const uint64_t *skeys, int8_t *lcp,
-                                                        uint8_t *depth, uint32_t *nstart) {
+                                                        uint8_t *depth, uint32_t *nstart, uint32_t *partial) {
+  __shared__ uint32_t tmp[kWaves];
   extern __shared__ int8_t sl[];  // lcp of particles lo .. lo + kThreads + 2 lmax
   const int64_t p0 = (int64_t)blockIdx.x * kThreads, lo = p0 - lmax;
   const int cnt = kThreads + 2 * lmax + 1;
@@ -735,13 +721,39 @@ __global__ __launch_bounds__(kThreads) void k_lcp_depth(const BoxDev *boxes, int
   }
   __syncthreads();
   const uint32_t p = (uint32_t)p0 + threadIdx.x;
-  if (p >= n) return;
-  const int lm = boxes[box_of(boxes, B, p)].leaf_max;
-  const int8_t *L = sl + (p - lo);  // L[j] = lcp(p + j)
-  const int own = L[0], d = leaf_depth(p, lm, [&](int j) { return (int)L[j]; });
-  lcp[p] = (int8_t)own;
-  depth[p] = (uint8_t)d;
-  nstart[p] = (uint32_t)max(0, d - own);
+  uint32_t starts = 0;
+  if (p < n) {
+    const int lm = boxes[box_of(boxes, B, p)].leaf_max;
+    const int8_t *L = sl + (p - lo);  // L[j] = lcp(p + j)
+    const int own = L[0], d = leaf_depth(p, lm, [&](int j) { return (int)L[j]; });
+    lcp[p] = (int8_t)own;
+    depth[p] = (uint8_t)d;
+    starts = (uint32_t)max(0, d - own);
+    nstart[p] = starts;
+  }
+  // the scan's tile sums (cleared by k_init_scalars)
+  uint32_t tot;
+  block_exscan(starts, tmp, &tot);
+  if (threadIdx.x == 0) atomicAdd(&partial[(uint32_t)p0 / kScanTile], tot);
+}
+
+// Node ranks: the scan of nstart.  A single box's node range and root are set
+// here too (single); a batch's by k_box_nodes.
+__global__ __launch_bounds__(kThreads) void k_node_ranks(const uint32_t *nstart, uint32_t *S, uint32_t n,
+                                                         const uint32_t *partial, BoxDev *single, uint32_t node_cap,
+                                                         uint32_t *scalars, uint32_t *parent, uint32_t *sib) {
+  __shared__ uint32_t buf[kScanTile];
+  __shared__ uint32_t tmp[kWaves];
+  const uint32_t tot = scan_tiles(
+      n, partial, buf, tmp, [&](uint32_t e) { return nstart[e]; }, [&](uint32_t e, uint32_t o) { S[e] = o; });
+  if (blockIdx.x != gridDim.x - 1 || threadIdx.x != 0) return;
+  S[n] = tot;
+  if (!single) return;
+  single->root = 0;
+  single->node_end = scalars[3] = min(tot, node_cap);
+  if (tot > node_cap) atomicOr(&scalars[0], kStatusNodes);
+  parent[0] = 0xffffffffu;
+  sib[0] = 0;
 }
 
 // Per box: node range [S[p_off], S[p_off+n]).
@@ -981,6 +993,11 @@ struct ChildSums {
     lo = l < lo ? l : lo;
   }
 };
+
+// The node's moments from its sums.
+__device__ inline Mom64 child_mom(const ChildSums &cs) {
+  return Mom64{cs.c[0] + cs.q0 / cs.M, cs.c[1] + cs.q1 / cs.M, cs.c[2] + cs.q2 / cs.M, cs.M};
+}
 
 // Node after the last node of r's subtree (pre-order).
 __device__ inline uint32_t subtree_end(const Topo &t, uint32_t r, uint32_t tot) {
@@ -1233,12 +1250,31 @@ __global__ __launch_bounds__(kThreads) void k_moments_segments(const BoxDev *box
           if (nx <= c) break;  // never taken for a well-formed tree
           c = nx;
         }
-        smom[i] = store_node(bx, tk, r, cs.c, cs.M, cs.q0, cs.q1, cs.q2, mom64, mom32, wn, cen64);
+        smom[i] = child_mom(cs);
         if (semax) {
           semax[r] = cs.hi;
           semin[r] = cs.lo;
         }
       }
+    }
+    // the records once the levels are done: a level's chain is its sums and
+    // divisions only
+    uint32_t todo = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kSegPer; ++k)
+      if (mine[k] && !(t[k].corner & kLeafBit)) todo |= 1u << k;
+    while (todo) {
+      const uint32_t k = __builtin_ctz(todo);
+      todo &= todo - 1;
+      Topo tk = t[0];
+#pragma unroll
+      for (uint32_t q = 1; q < kSegPer; ++q)
+        if (k == q) tk = t[q];
+      const uint32_t i = threadIdx.x + k * kThreads, r = base + i;
+      const BoxDev &bx = node_box(boxes, B, first, r);
+      double c[3];
+      node_centre(bx, tk.corner, (int)(tk.b >> kCountBits), c);
+      node_records(bx, tk, r, c, smom[i], mom64, mom32, wn, cen64);
     }
   }
 }
@@ -1265,17 +1301,6 @@ __device__ inline void sort_slots(uint64_t sl[8]) {
         sl[j] = sl[j - 1];
         sl[j - 1] = u;
       }
-}
-
-__device__ inline Mom64 top_mom(const ChildSums &cs) {
-  return Mom64{cs.c[0] + cs.q0 / cs.M, cs.c[1] + cs.q1 / cs.M, cs.c[2] + cs.q2 / cs.M, cs.M};
-}
-
-__device__ inline void top_records(const BoxDev &bx, const Topo &t, uint32_t r, const double c[3],
-                                   const Mom64 &m, Mom32 *mom32, WNode *wn, double4 *cen64) {
-  const Mom32 m32{(float)(m.cx - c[0]), (float)(m.cy - c[1]), (float)(m.cz - c[2]), (float)m.m};
-  mom32[r] = m32;
-  walk_records(bx, t, m32, r, wn, cen64);
 }
 
 __global__ __launch_bounds__(kTopThreads) void k_moments_top(const BoxDev *boxes, int B, const Topo *topo,
@@ -1318,11 +1343,10 @@ __global__ __launch_bounds__(kTopThreads) void k_moments_top(const BoxDev *boxes
         if ((uint32_t)sl[q] & kTopRef) m[q] = smt[(uint32_t)sl[q] & ~kTopRef];
         cs.add(m[q]);
       }
-      const Mom64 mr = top_mom(cs);
-      smt[i] = mr;
-      mom64[r] = mr;
-      top_records(node_box(boxes, B, first, r), t, r, cs.c, mr, mom32, wn, cen64);
+      smt[i] = child_mom(cs);
     }
+    if (own)  // the records after the levels, as in k_moments_segments
+      node_records(node_box(boxes, B, first, r), t, r, cs.c, smt[i], mom64, mom32, wn, cen64);
     return;
   }
   for (int L = hi; L >= 0; --L) {
@@ -1345,8 +1369,7 @@ __global__ __launch_bounds__(kTopThreads) void k_moments_top(const BoxDev *boxes
 #pragma unroll
       for (int q = 0; q < 8; ++q)
         if (sl[q] != ~0ull) cs.add(m[q]);
-      const Mom64 mr = top_mom(cs);
-      mom64[r] = mr;
+      const Mom64 mr = child_mom(cs);
       if (semax) {
 #pragma unroll
         for (int q = 0; q < 8; ++q)
@@ -1357,7 +1380,7 @@ __global__ __launch_bounds__(kTopThreads) void k_moments_top(const BoxDev *boxes
         semax[r] = cs.hi;
         semin[r] = cs.lo;
       }
-      top_records(bx, topo[r], r, cs.c, mr, mom32, wn, cen64);
+      node_records(bx, topo[r], r, cs.c, mr, mom64, mom32, wn, cen64);
     }
   }
 }
@@ -1613,7 +1636,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(BuildArrays A, So
       ChildSums cs;
       node_centre(bx, t[k].corner, L, cs.c);
       for (uint32_t q = 0; q < kids[k]; ++q) cs.add(u.mom[kid16[first_kid[k] + q]]);
-      u.mom[r] = top_mom(cs);
+      u.mom[r] = child_mom(cs);
     }
   }
 #pragma unroll 1
@@ -1664,17 +1687,20 @@ __global__ void k_reset(uint32_t *w) { *w = 0; }
 __global__ void k_reset_queues(uint32_t *counter) {
   if (threadIdx.x < kQueues) counter[threadIdx.x * kQueueStride] = 0;
 }
-// Status word cleared, particle count for the device-side scans, counters
-// of the top-node lists cleared, child slots from B on (the roots' come first).
-__global__ void k_init_scalars(uint32_t *sc, uint32_t n, uint32_t *top_cnt, int B) {
+// Status word cleared, particle count, counters of the top-node lists and the
+// scan's tile sums cleared, child slots from B on (the roots' come first).
+__global__ __launch_bounds__(kThreads) void k_init_scalars(uint32_t *sc, uint32_t n, uint32_t *top_cnt, int B,
+                                                           uint32_t *partial) {
   if (threadIdx.x == 0) {
     sc[0] = 0u;
     sc[4] = n;
   }
   if (threadIdx.x < 4) top_cnt[threadIdx.x] = threadIdx.x == 1 ? (uint32_t)B : 0u;
+  for (uint32_t i = threadIdx.x; i <= n / kScanTile; i += kThreads) partial[i] = 0;
 }
 
 inline uint32_t cdiv(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b); }
+inline uint32_t scan_grid(uint32_t n) { return std::max<uint32_t>(1, std::min<uint32_t>(cdiv(n, kScanTile), kScanGrid)); }
 
 int g_cu = 0;
 
@@ -1699,14 +1725,6 @@ void launch_max_level(const BuildArrays &A, uint32_t *out, hipStream_t s) {
   k_reset<<<1, 1, 0, s>>>(out);
   const uint32_t g = std::max<uint32_t>(1, std::min<uint32_t>(cdiv(A.node_cap, kThreads), 1024));
   k_max_level<<<g, kThreads, 0, s>>>(A.topo, A.scalars, A.node_cap, out);
-}
-
-void scan_u32(const uint32_t *in, uint32_t *out, const uint32_t *n_dev, uint32_t cap,
-              uint32_t *partial, hipStream_t s) {
-  const uint32_t nb = cdiv((uint64_t)cap + 1, kScanTile);
-  k_scan_reduce<<<nb, kThreads, 0, s>>>(in, n_dev, partial);
-  k_scan_partials<<<1, kThreads, 0, s>>>(partial, n_dev);
-  k_scan_down<<<nb, kThreads, 0, s>>>(in, out, n_dev, partial);
 }
 
 size_t radix_hist_words(uint32_t n) { return (size_t)256 * cdiv(n > 0 ? n : 1, kSortTile); }
@@ -1786,7 +1804,7 @@ void launch_build(BuildArrays &A, hipStream_t s) {
   // one box whose nodes fit one workgroup's LDS (1232 particles with leaves of
   // up to 8); per-particle lengths take the general path
   const bool small = A.B == 1 && !A.seps && n <= kSmallN && A.node_cap <= kSmallNodes && !env_set("OG_NO_SMALL_BUILD");
-  if (!small || A.any_open) k_init_scalars<<<1, 64, 0, s>>>(A.scalars, n, A.top_cnt, A.B);
+  if (!small || A.any_open) k_init_scalars<<<1, kThreads, 0, s>>>(A.scalars, n, A.top_cnt, A.B, A.scan_partial);
   if (A.any_open) {
     k_frame_init<<<cdiv(6 * (uint64_t)A.B, kThreads), kThreads, 0, s>>>(A.B, A.minmax);
     // at most 256 workgroups: 1536 atomics on one box's six words
@@ -1827,9 +1845,11 @@ void launch_build(BuildArrays &A, hipStream_t s) {
   {
     const TraceRange r("build: topology");
     k_lcp_depth<<<nb, kThreads, kThreads + 2 * A.leaf_max + 1, s>>>(A.boxes, A.B, n, A.leaf_max, skeys, A.lcp,
-                                                                    A.depth, A.nstart);
-    scan_u32(A.nstart, A.S, &A.scalars[4], n, A.scan_partial, s);
-    k_box_nodes<<<cdiv(A.B, 64), 64, 0, s>>>(A.boxes, A.B, A.S, n, A.node_cap, A.scalars, A.parent, A.sib);
+                                                                    A.depth, A.nstart, A.scan_partial);
+    k_node_ranks<<<scan_grid(n), kThreads, 0, s>>>(A.nstart, A.S, n, A.scan_partial, A.B == 1 ? A.boxes : nullptr,
+                                                         A.node_cap, A.scalars, A.parent, A.sib);
+    if (A.B > 1)
+      k_box_nodes<<<cdiv(A.B, 64), 64, 0, s>>>(A.boxes, A.B, A.S, n, A.node_cap, A.scalars, A.parent, A.sib);
     k_emit<<<nb, kThreads, 0, s>>>(A.boxes, A.B, n, skeys, A.lcp, A.depth, A.S, A.node_cap, A.topo,
                                    A.first, A.skip);
     k_links<<<glinks, kLinkThreads, 0, s>>>(A.topo, A.skip, A.scalars, A.node_cap, A.parent, A.kid, A.sib, A.top_cnt + 1);
@@ -1855,39 +1875,61 @@ void launch_build(BuildArrays &A, hipStream_t s) {
 
 
 // Active targets (see ActiveArrays).  Flags and the compaction run over the
-// sorted order, so the active list keeps the curve order of the tree.
+// sorted order, so the active list keeps the curve order of the tree.  A
+// workgroup flags a scan tile and leaves its sum, then scans and scatters it.
 __global__ __launch_bounds__(kThreads) void k_active_flags(const uint32_t *perm, const int8_t *bin,
-                                                           int32_t level, uint32_t n, uint32_t *flags) {
-  const uint32_t p = blockIdx.x * kThreads + threadIdx.x;
-  if (p >= n) return;
-  flags[p] = (int32_t)bin[perm[p]] <= level ? 1u : 0u;
+                                                           int32_t level, uint32_t n, uint8_t *flags,
+                                                           uint32_t *partial) {
+  __shared__ uint32_t tmp[kWaves];
+  uint32_t c = 0;
+  for (uint32_t i = threadIdx.x; i < kScanTile; i += 8 * kThreads) {
+    uint32_t q[8];
+    int32_t v[8];
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) q[k] = perm[min(blockIdx.x * kScanTile + i + k * kThreads, n - 1u)];
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) v[k] = bin[q[k]];
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) {
+      const uint32_t p = blockIdx.x * kScanTile + i + k * kThreads;
+      if (p >= n) continue;
+      const uint32_t on = v[k] <= level ? 1u : 0u;
+      flags[p] = (uint8_t)on;
+      c += on;
+    }
+  }
+  uint32_t tot;
+  block_exscan(c, tmp, &tot);
+  if (threadIdx.x == 0) partial[blockIdx.x] = tot;
 }
 
-__global__ __launch_bounds__(kThreads) void k_active_scatter(const uint32_t *flags, const uint32_t *offs,
+__global__ __launch_bounds__(kThreads) void k_active_scatter(const uint8_t *flags, const uint32_t *partial,
                                                              const uint32_t *perm, uint32_t n, uint32_t chunk,
                                                              uint64_t *tkey, uint32_t *tval, uint32_t *counts,
                                                              int64_t *n_active) {
-  const uint32_t p = blockIdx.x * kThreads + threadIdx.x;
-  if (p == 0) {
-    const uint32_t m = offs[n];
+  __shared__ uint32_t buf[kScanTile];
+  __shared__ uint32_t tmp[kWaves];
+  const uint32_t m = scan_tiles(
+      n, partial, buf, tmp, [&](uint32_t e) { return (uint32_t)flags[e]; },
+      [&](uint32_t e, uint32_t o) {
+        if (!flags[e]) return;
+        tkey[o] = e;
+        tval[o] = perm[e];
+      });
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
     counts[0] = m;
     counts[1] = (m + chunk - 1) / chunk;
     if (n_active) *n_active = (int64_t)m;
   }
-  if (p >= n || !flags[p]) return;
-  const uint32_t o = offs[p];
-  tkey[o] = p;
-  tval[o] = perm[p];
 }
 
-size_t scan_partial_words(uint32_t n) { return cdiv((uint64_t)n + 1, kScanTile) + 1; }
+size_t scan_partial_words(uint32_t n) { return cdiv(n, kScanTile) + 1; }
 
 void launch_active(const BuildArrays &A, ActiveArrays &T, uint32_t chunk, hipStream_t s) {
   const uint32_t n = A.n;
-  k_active_flags<<<cdiv(n, kThreads), kThreads, 0, s>>>(A.perm, T.bin, T.level, n, T.flags);
-  scan_u32(T.flags, T.offs, &A.scalars[4], n, T.partial, s);
-  k_active_scatter<<<cdiv(n, kThreads), kThreads, 0, s>>>(T.flags, T.offs, A.perm, n, chunk, T.tkey, T.tval,
-                                                         T.counts, T.n_active);
+  k_active_flags<<<cdiv(n, kScanTile), kThreads, 0, s>>>(A.perm, T.bin, T.level, n, T.flags, T.partial);
+  k_active_scatter<<<scan_grid(n), kThreads, 0, s>>>(T.flags, T.partial, A.perm, n, chunk, T.tkey, T.tval, T.counts,
+                                             T.n_active);
 }
 
 void launch_targets(const BuildArrays &A, TargetArrays &T, hipStream_t s) {

@@ -423,8 +423,7 @@ int Forest::walk_active(int prec, hipStream_t s, const int8_t *bin, int32_t leve
                         int64_t *nint, const double *a_old, int64_t *n_active) {
   ActiveArrays T{};
   auto plan = [&](Carver &cv) {
-    T.flags = cv.take<uint32_t>(N);
-    T.offs = cv.take<uint32_t>((size_t)N + 1);
+    T.flags = cv.take<uint8_t>(N);
     T.partial = cv.take<uint32_t>(scan_partial_words(N));
     T.tkey = cv.take<uint64_t>(N);
     T.tval = cv.take<uint32_t>(N);

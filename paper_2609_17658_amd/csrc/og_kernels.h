@@ -6,11 +6,9 @@
 
 namespace og {
 
-// Exclusive scan of n = *n_dev (device scalar, <= cap) uint32 values:
-// out[0..n] with out[n] = total.  `partial` holds cap/kScanTile + 2 words.
+// Tile of the scans (node ranks, active targets); scan_partial_words(n) tile
+// sums each.
 constexpr uint32_t kScanTile = 4096;
-void scan_u32(const uint32_t *in, uint32_t *out, const uint32_t *n_dev, uint32_t cap,
-              uint32_t *partial, hipStream_t s);
 
 // LSD radix sort of (key, val) pairs, 8-bit digits.  Key passes
 // [pass_lo, pass_hi) on the 64-bit key, then `box_passes` passes on the box
@@ -106,7 +104,8 @@ void launch_targets(const BuildArrays &A, TargetArrays &T, hipStream_t s);
 struct ActiveArrays {
   const int8_t *bin;
   int32_t level;
-  uint32_t *flags, *offs, *partial;
+  uint8_t *flags;
+  uint32_t *partial;
   uint64_t *tkey;
   uint32_t *tval;
   uint32_t *counts;           // [0] active, [1] groups, [32..] walk queues (kScalarWords in all)
