@@ -873,9 +873,24 @@ __device__ inline float leaf_tag(uint32_t first, uint32_t n, bool wrap) {
   return __uint_as_float(leaf_tag_bits(first, n, wrap));
 }
 
-// Evaluate and empty every lane's list, lane-parallel: each step every lane
-// takes the next partner of its own list (a monopole, or the next particle
-// of a leaf entry, read with a per-lane load), in list order.
+// Evaluate and empty every lane's list, lane-parallel: each row every lane
+// takes the next partners of its own list (a monopole, or the next particles
+// of a leaf entry, read with per-lane loads), in list order.
+// The vector issue bounds this: in a Zel'dovich box three quarters of a
+// walk's instructions are here, 1096 rows a group of one partner each, 1091 of
+// them leaf particles in 16 of 64 lanes.  So a row takes two particles of the
+// leaf for one reading of the entry, whose loads are in flight together, at
+// 32-bit offsets from the scalar base; and lanes leave the loop one by one
+// (asking whether any is left costs copies of the sums in every row).  Rows
+// that hold one entry of every lane, its particles in an inner loop, carry
+// less and are 6 % faster where the leaves are all full, but 3 to 10 % slower
+// where their counts differ (487k mixture, 78^3 Zel'dovich): lanes wait for the
+// longest leaf of each row.  Measured, walk only: 16.8M Zel'dovich 20.5 -> 17.4
+// ms, 2M of it 2.78 -> 2.45, 262144 0.73 -> 0.65; 2M mixture 5.23 -> 5.15;
+// 100k isolated 1.80 -> 1.68.
+// The kExt variants take one particle a row: their terms are long, and a
+// second copy of them loses more (487k with spline, relative criterion and
+// lengths 2.69 | 2.56 ms).
 // A lane's list position is kept as the byte offset of its slot in `list`
 // (row * kListRow + lane * 16), which is the LDS address the slot's load or
 // store takes, so that no address is formed per entry.
@@ -887,12 +902,13 @@ __device__ inline float4 &list_at(float4 (*list)[kWalk32Threads], uint32_t off) 
 template <int kCap, bool kExt, bool kSoft>
 __device__ inline void flush(const WalkArgs &A, float4 (*list)[kWalk32Threads], float (*lsoft)[kWalk32Threads],
                              float eif, uint32_t lane, uint32_t p, uint32_t &cnt, const Consts32 &k, double &ax,
-                             double &ay, double &az, double &ph, uint32_t &ni) {
+                             double &ay, double &az, double &ph, uint32_t &ni, uint32_t &wraps) {
 #pragma clang fp contract(fast)
   // cnt: this lane's next free slot (byte offset); e: the entry being read
-  uint32_t e = lane * (uint32_t)sizeof(float4), j = 0;
-  while (__ballot(e < cnt)) {
-    if (e < cnt) {
+  if constexpr (kExt) {
+    // every lane its next partner of either kind
+    uint32_t e = lane * (uint32_t)sizeof(float4), j = 0;
+    while (e < cnt) {
       const float4 q = list_at(list, e);
       const uint32_t tag = __float_as_uint(q.w);
       float dx = q.x, dy = q.y, dz = q.z, m = q.w;
@@ -931,7 +947,69 @@ __device__ inline void flush(const WalkArgs &A, float4 (*list)[kWalk32Threads], 
         ++ni;
       }
     }
+  } else {
+    constexpr uint32_t kP = (uint32_t)sizeof(float4);
+    const uint32_t self = p * kP;
+    uint32_t e = lane * kP, j = 0;
+    const auto part = [&](uint32_t o) {
+      return *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(A.part32) + o);
+    };
+    while (e < cnt) {
+      const float4 q = list_at(list, e);
+      const uint32_t tag = __float_as_uint(q.w);
+      float dx = q.x, dy = q.y, dz = q.z, m = q.w, r2;
+      float ex, ey, ez, m2, s2;
+      bool use = true, use2 = false;
+      if (tag & kTagLeaf) {
+        const uint32_t n1 = ((tag >> 27) & 7u) * kP;
+        const bool two = j < n1;
+        uint32_t off = (__builtin_amdgcn_ubfe(tag, 0, 27) << 4) + j;
+        uint32_t o1 = off + (two ? kP : 0u);
+        asm("" : "+v"(off), "+v"(o1));  // kept 32-bit offsets, not made 64-bit addresses
+        const float4 pa = part(off), pb = part(o1);
+        ex = dx + pb.x;
+        ey = dy + pb.y;
+        ez = dz + pb.z;
+        dx += pa.x;
+        dy += pa.y;
+        dz += pa.z;
+        if (wraps) {  // rare; the empty asm keeps it a branch of its own
+          asm volatile("");
+          if (tag & kTagWrap) {
+            dx = wrap_box(dx, k);
+            dy = wrap_box(dy, k);
+            dz = wrap_box(dz, k);
+            ex = wrap_box(ex, k);
+            ey = wrap_box(ey, k);
+            ez = wrap_box(ez, k);
+          }
+        }
+        m = pa.w;
+        m2 = pb.w;
+        r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+        s2 = fmaf(ez, ez, fmaf(ey, ey, ex * ex));
+        use = off != self && (!k.cutoff || r2 < k.rc2);
+        use2 = two && o1 != self && (!k.cutoff || s2 < k.rc2);
+        j += 2u * kP;
+        if (j > n1) {
+          j = 0;
+          e += kListRow;
+        }
+      } else {
+        r2 = fmaf(dz, dz, fmaf(dx, dx, dy * dy));
+        e += kListRow;
+      }
+      if (use) {
+        eval32<false>(dx, dy, dz, r2, m, k, ax, ay, az, ph);
+        ++ni;
+      }
+      if (use2) {
+        eval32<false>(ex, ey, ez, s2, m2, k, ax, ay, az, ph);
+        ++ni;
+      }
+    }
   }
+  wraps = 0;
   cnt = lane * (uint32_t)sizeof(float4);
 }
 
@@ -943,11 +1021,11 @@ __device__ inline void flush(const WalkArgs &A, float4 (*list)[kWalk32Threads], 
 // exceed 4 GiB); otherwise a record's byte offset is one 32-bit scalar
 // product, which the scalar load takes as its offset register.
 template <int kCap, int kMode, bool kExt, bool kSoft = false, bool kWide = false>
-// With 4-deep lists every variant fits 8 waves per SIMD (64 vector and at
-// most 96 scalar registers, no spills), which hides more latency than the
-// 7 that the scalar registers would otherwise allow.
+// With lists of up to 5 entries every variant fits 8 waves per SIMD (64 vector
+// and at most 96 scalar registers, no vector spills), which hides more latency
+// than the 7 that the scalar registers would otherwise allow.
 __global__ __launch_bounds__(kWalk32Threads)
-__attribute__((amdgpu_waves_per_eu(kCap == 4 ? 8 : 1, 8))) void k_walk32(WalkArgs A) {
+__attribute__((amdgpu_waves_per_eu(kCap <= 5 ? 8 : 1, 8))) void k_walk32(WalkArgs A) {
 #pragma clang fp contract(fast)
   __shared__ float4 list[kCap][kWalk32Threads];
   __shared__ float lsoft[kSoft ? kCap : 1][kWalk32Threads];  // monopoles' softening lengths
@@ -1025,6 +1103,7 @@ __attribute__((amdgpu_waves_per_eu(kCap == 4 ? 8 : 1, 8))) void k_walk32(WalkArg
     double ax = 0.0, ay = 0.0, az = 0.0, ph = 0.0;
     // cnt: the byte offset of this lane's next free list slot (see list_at)
     uint32_t ni = 0, cnt = lane * (uint32_t)sizeof(float4);
+    uint32_t wraps = 0;  // a listed leaf's offsets may need the minimum image
     const uint32_t cfull = cnt + kCap * kListRow;
     const uint32_t nend = bx.node_end;
     // A lane is active at node n while next <= n: an opening lane keeps its
@@ -1054,7 +1133,7 @@ __attribute__((amdgpu_waves_per_eu(kCap == 4 ? 8 : 1, 8))) void k_walk32(WalkArg
                               : ldw((const WNode *)((const char *)A.wnode + n * (uint32_t)sizeof(WNode)));
         const uint32_t cf = w.cf;
         // room for this visit's entry
-        if (__ballot(cnt >= cfull)) flush<kCap, kExt, kSoft>(A, list, lsoft, eif, lane, p, cnt, k, ax, ay, az, ph, ni);
+        if (__ballot(cnt >= cfull)) flush<kCap, kExt, kSoft>(A, list, lsoft, eif, lane, p, cnt, k, ax, ay, az, ph, ni, wraps);
         float f0, f1, f2;  // node centre minus lane origin, in half-cells (exact)
         if (kPer && kForm == 1) {
           f0 = biased((w.c[0] - gq0) & kMask) - qb0;
@@ -1080,6 +1159,7 @@ __attribute__((amdgpu_waves_per_eu(kCap == 4 ? 8 : 1, 8))) void k_walk32(WalkArg
         if (pend | (cf & (kWBig | (kPer ? kWWrap : 0u)))) {
           const uint32_t lc = cf & kWCount;
           const bool wrapd = kPer && (cf & kWWrap) != 0;
+          wraps |= cf & kWWrap;
           if (pend) {
             if (next <= n) {
               list_at(list, cnt) = make_float4(dcx + w.o[0], dcy + w.o[1], dcz + w.o[2],
@@ -1165,7 +1245,7 @@ __attribute__((amdgpu_waves_per_eu(kCap == 4 ? 8 : 1, 8))) void k_walk32(WalkArg
     if (kPer && lane_wrap) walk(std::integral_constant<int, 2>{});
     else if (kPer && !interior) walk(std::integral_constant<int, 1>{});
     else walk(std::integral_constant<int, 0>{});
-    flush<kCap, kExt, kSoft>(A, list, lsoft, eif, lane, p, cnt, k, ax, ay, az, ph, ni);
+    flush<kCap, kExt, kSoft>(A, list, lsoft, eif, lane, p, cnt, k, ax, ay, az, ph, ni, wraps);
     if (valid) write_out(A, bx, slot, ax, ay, az, ph, ni);
   }
 }
@@ -2301,7 +2381,11 @@ void launch_walk(const WalkArgs &W0, int precision, hipStream_t s) {
     else if (W.erfc_tail) k_walk64<false, true><<<blocks, 64 * kWalk64Waves, 0, s>>>(W);
     else k_walk64<false, false><<<blocks, 64 * kWalk64Waves, 0, s>>>(W);
   } else {
-    // one wave per workgroup; LDS per wave = cap x 1 KB of lists
+    // one wave per workgroup; LDS per wave = cap x 1 KB of lists.  The shortest
+    // lists (4) get a fifth entry where no softening lengths are listed: 32
+    // waves of 5 KB are exactly a CU's LDS, and fuller rows of the evaluation
+    // cost no wave (16.8M Zel'dovich particles 17.2 -> 16.9 ms, 2M mixture the
+    // same; 6 entries at 6 waves lose 10 %).
     const int cap = W.list_cap > 0 ? W.list_cap : walk_list_capacity();
     const uint32_t per_cu = std::min<uint32_t>(32u, 160u / (uint32_t)cap);
     const uint32_t blocks = std::max<uint32_t>(1, std::min<uint32_t>(per_cu * cus, groups));
@@ -2311,7 +2395,7 @@ void launch_walk(const WalkArgs &W0, int precision, hipStream_t s) {
   do {                                                                               \
     if (wide && W.seps) k_walk32<4, 0, true, true, true><<<blocks, kWalk32Threads, 0, s>>>(W); \
     else if (wide) k_walk32<4, 0, true, false, true><<<blocks, kWalk32Threads, 0, s>>>(W); \
-    else if (W.seps) k_walk32<C, 0, true, true><<<blocks, kWalk32Threads, 0, s>>>(W); \
+    else if (W.seps) k_walk32<C == 5 ? 4 : C, 0, true, true><<<blocks, kWalk32Threads, 0, s>>>(W); \
     else if (W.ext) k_walk32<C, 0, true><<<blocks, kWalk32Threads, 0, s>>>(W);       \
     else if (mode == 2) k_walk32<C, 2, false><<<blocks, kWalk32Threads, 0, s>>>(W);  \
     else if (mode == 1) k_walk32<C, 1, false><<<blocks, kWalk32Threads, 0, s>>>(W);  \
@@ -2319,7 +2403,7 @@ void launch_walk(const WalkArgs &W0, int precision, hipStream_t s) {
     else k_walk32<C, 0, false><<<blocks, kWalk32Threads, 0, s>>>(W);                 \
   } while (0)
     if (cap == 8) OG_WALK32(8);
-    else if (cap == 4) OG_WALK32(4);
+    else if (cap == 4) OG_WALK32(5);
     else if (cap == 32) OG_WALK32(32);
     else OG_WALK32(16);
 #undef OG_WALK32
