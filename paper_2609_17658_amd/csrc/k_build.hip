@@ -72,7 +72,9 @@ __device__ inline uint32_t sum_partials(const uint32_t *partial, uint32_t count,
 // get(e) is value e, put(e, o) takes its offset o.  A workgroup adds up the sums
 // of the tiles before its run of tiles (from L2; at most kScanGrid runs) instead
 // of waiting for a launch that scans them.  Returns the offset after the run:
-// in the last workgroup, the total.
+// in the last workgroup, the total.  (Tile sums, their scan and the tiles as
+// three launches: with the root's launch 13 us more of each build up to 1e6
+// particles, 5 us of an active walk; at 16.8M the same.)
 constexpr uint32_t kScanGrid = 2048;
 
 template <class Get, class Put>
@@ -1756,7 +1758,7 @@ static bool env_set(const char *name) {
 
 // Whether boxes of up to `longest` particles (n in all), or a list of n
 // targets, take the merge sort.  Measured against the radix sort, build of
-// one box (us, clustered): 1e3 204|102, 3.3e4 282|167, 2.6e5 319|230, 5.1e5
+// one box (us, clustered): 1e3 204|102 (now k_build_small's), 3.3e4 282|167, 2.6e5 319|230, 5.1e5
 // 368|309, 1e6 450|511, 2.1e6 662|944: its searches grow with the size and
 // cost more than launches from 6e5 on, and from 1.5e6 in a batch (which saves
 // the passes over box numbers too: 1.4e6 in 32 boxes 4.19|4.09 ms with the
