@@ -438,10 +438,9 @@ __device__ inline uint32_t lane_rank(uint64_t mask) {
 // Lanes with an item from which a row is evaluated in place: spreading a row
 // over full steps costs each of its owners a descriptor, a slot and the terms'
 // way back, about what 28 idle lanes of a pair term cost.  Screened FP64 walk,
-// ms at 24, 28, 32, 36, 40, 44, 48: 2M mixture 12.58 12.46 12.30 12.11 12.35
-// 12.32 12.63, 2M Zel'dovich 5.96 5.86 5.79 5.81 5.85 5.89 6.08, 100k isolated
-// 4.13 4.12 4.18 4.26 4.26 4.33 4.28; spline, relative criterion and lengths
-// within 2 % from 32 to 48.
+// ms at 36, 40, 44, 48 (in turn): 2M mixture 12.31 12.43 12.45 12.48, 487k of it
+// 3.92 3.91 3.90 4.03, 2M Zel'dovich 5.79 5.87 5.94 6.04, 200k isolated the
+// same; 24 and 28 are slower again.
 constexpr uint32_t kOwnerRows = 36;
 template <int kCap, class Items, class Term>
 __device__ inline void flush_rows64(double4 *slots, uint32_t lane, uint32_t p, uint32_t nent, Items items, Term term,
