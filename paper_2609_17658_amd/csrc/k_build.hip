@@ -910,8 +910,9 @@ __device__ inline void node_centre(const BoxDev &bx, uint64_t corner, int level,
   c[2] = bx.lo[2] + ((double)(uint32_t)((corner >> 42) & 0x1fffffull) + half) * h;
 }
 
-// Walk record (see WNode) and FP64 cube centre and side of node r.
-__device__ inline void walk_records(const BoxDev &bx, const Topo &t, const Mom32 &m, uint32_t r, WNode *wn,
+// Walk record (see WNode) and FP64 cube centre and side of node r; m: its
+// centre of mass's FP32 offset from the cube centre, and its mass.
+__device__ inline void walk_records(const BoxDev &bx, const Topo &t, const float4 m, uint32_t r, WNode *wn,
                                     double4 *cen64) {
   const int lev = (int)(t.b >> kCountBits);
   const int hc = 1 << (kLevels - lev);
@@ -923,10 +924,10 @@ __device__ inline void walk_records(const BoxDev &bx, const Topo &t, const Mom32
   w.c[2] = 0x4B000000 | (2 * (int)((t.corner >> 42) & 0x1fffffull) + hc);
   // the geometric criterion side^2 > theta^2 r^2 as one comparison with r^2
   w.side2 = bx.relative ? side * side : (bx.theta2f > 0.0f ? side * side / bx.theta2f : INFINITY);
-  w.o[0] = m.ox;
-  w.o[1] = m.oy;
-  w.o[2] = m.oz;
-  w.m = bx.Gf * m.m;  // G M: the FP32 pair term's factor
+  w.o[0] = m.x;
+  w.o[1] = m.y;
+  w.o[2] = m.z;
+  w.m = bx.Gf * m.w;  // G M: the FP32 pair term's factor
   w.reach = bx.rcutf + 0.5f * side;
   w.near = 0.6f * side;
   const uint32_t count = t.b & kCountMask;
@@ -943,23 +944,22 @@ __device__ inline void walk_records(const BoxDev &bx, const Topo &t, const Mom32
                           ldexp(bx.L, -lev));
 }
 
-// Node r's moments m (cube centre c): FP64 and FP32 forms, then the walk
-// records.
+// Node r's moments m (cube centre c), then the walk records, which hold their
+// FP32 form.
 __device__ inline void node_records(const BoxDev &bx, const Topo &t, uint32_t r, const double c[3], const Mom64 &m,
-                                    Mom64 *mom64, Mom32 *mom32, WNode *wn, double4 *cen64) {
+                                    Mom64 *mom64, WNode *wn, double4 *cen64) {
   mom64[r] = m;
-  const Mom32 m32{(float)(m.cx - c[0]), (float)(m.cy - c[1]), (float)(m.cz - c[2]), (float)m.m};
-  mom32[r] = m32;
-  walk_records(bx, t, m32, r, wn, cen64);
+  walk_records(bx, t, make_float4((float)(m.cx - c[0]), (float)(m.cy - c[1]), (float)(m.cz - c[2]), (float)m.m), r, wn,
+               cen64);
 }
 
 // Mass and centre of mass of node r from its mass M and first moments s
 // about the cube centre c, and its records.
 __device__ inline Mom64 store_node(const BoxDev &bx, const Topo &t, uint32_t r, const double c[3], double M,
-                                   double s0, double s1, double s2, Mom64 *mom64, Mom32 *mom32, WNode *wn,
+                                   double s0, double s1, double s2, Mom64 *mom64, WNode *wn,
                                    double4 *cen64) {
   const Mom64 m{c[0] + s0 / M, c[1] + s1 / M, c[2] + s2 / M, M};
-  node_records(bx, t, r, c, m, mom64, mom32, wn, cen64);
+  node_records(bx, t, r, c, m, mom64, wn, cen64);
   return m;
 }
 
@@ -1048,7 +1048,7 @@ __device__ inline uint32_t octant(const Topo &t) {
 
 __global__ __launch_bounds__(kThreads) void k_moments_leaves(const BoxDev *boxes, int B, const Topo *topo,
                                                              const uint32_t *parent, const double4 *part64,
-                                                             float4 *part32, Mom64 *mom64, Mom32 *mom32,
+                                                             float4 *part32, Mom64 *mom64,
                                                              WNode *wn, double4 *cen64, uint32_t *scalars,
                                                              uint32_t node_cap, TopArrays T, const double *seps,
                                                              double *semax, double *semin) {
@@ -1122,7 +1122,7 @@ __global__ __launch_bounds__(kThreads) void k_moments_leaves(const BoxDev *boxes
       } else {
         for (uint32_t j = f; j < f + cnt; ++j) leaf_add(part64[j], c, M, s0, s1, s2);
       }
-      const Mom64 m = store_node(bx, t, r, c, M, s0, s1, s2, mom64, mom32, wn, cen64);
+      const Mom64 m = store_node(bx, t, r, c, M, s0, s1, s2, mom64, wn, cen64);
       if (staged) {
         for (uint32_t j = f; j < f + cnt; ++j) part32[j] = leaf_offset(stage[j - pa], m, bx.Gf);
       } else {
@@ -1143,7 +1143,7 @@ __global__ __launch_bounds__(kThreads) void k_moments_leaves(const BoxDev *boxes
 
 __global__ __launch_bounds__(kThreads) void k_moments_segments(const BoxDev *boxes, int B, const Topo *topo,
                                                                const uint32_t *first, const uint32_t *parent,
-                                                               const uint32_t *cls, Mom64 *mom64, Mom32 *mom32,
+                                                               const uint32_t *cls, Mom64 *mom64,
                                                                WNode *wn, double4 *cen64, const uint32_t *scalars,
                                                                uint32_t node_cap, TopArrays T, double *semax,
                                                                double *semin) {
@@ -1276,7 +1276,7 @@ __global__ __launch_bounds__(kThreads) void k_moments_segments(const BoxDev *box
       const BoxDev &bx = node_box(boxes, B, first, r);
       double c[3];
       node_centre(bx, tk.corner, (int)(tk.b >> kCountBits), c);
-      node_records(bx, tk, r, c, smom[i], mom64, mom32, wn, cen64);
+      node_records(bx, tk, r, c, smom[i], mom64, wn, cen64);
     }
   }
 }
@@ -1288,8 +1288,7 @@ __global__ __launch_bounds__(kThreads) void k_moments_segments(const BoxDev *box
 // kTopThreads top nodes every thread holds one, its slots and its segment
 // -root children's moments in registers, and the top nodes' moments stay
 // in LDS, so the levels cost no memory round trip; larger sets read slots
-// and moments from global memory at every level.  FP32 moments and walk
-// records follow.
+// and moments from global memory at every level.  Walk records follow.
 constexpr int kTopThreads = 1024;
 
 // A node's slots in child order (empty slots, all ones, sort last).
@@ -1306,7 +1305,7 @@ __device__ inline void sort_slots(uint64_t sl[8]) {
 }
 
 __global__ __launch_bounds__(kTopThreads) void k_moments_top(const BoxDev *boxes, int B, const Topo *topo,
-                                                             const uint32_t *first, Mom64 *mom64, Mom32 *mom32,
+                                                             const uint32_t *first, Mom64 *mom64,
                                                              WNode *wn, double4 *cen64, TopArrays T,
                                                              double *semax, double *semin) {
   __shared__ Mom64 smt[kTopThreads];
@@ -1348,7 +1347,7 @@ __global__ __launch_bounds__(kTopThreads) void k_moments_top(const BoxDev *boxes
       smt[i] = child_mom(cs);
     }
     if (own)  // the records after the levels, as in k_moments_segments
-      node_records(node_box(boxes, B, first, r), t, r, cs.c, smt[i], mom64, mom32, wn, cen64);
+      node_records(node_box(boxes, B, first, r), t, r, cs.c, smt[i], mom64, wn, cen64);
     return;
   }
   for (int L = hi; L >= 0; --L) {
@@ -1382,7 +1381,7 @@ __global__ __launch_bounds__(kTopThreads) void k_moments_top(const BoxDev *boxes
         semax[r] = cs.hi;
         semin[r] = cs.lo;
       }
-      node_records(bx, topo[r], r, cs.c, mr, mom64, mom32, wn, cen64);
+      node_records(bx, topo[r], r, cs.c, mr, mom64, wn, cen64);
     }
   }
 }
@@ -1647,7 +1646,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(BuildArrays A, So
     const Mom64 m = u.mom[r];
     double c[3];
     node_centre(bx, tr.corner, (int)(tr.b >> kCountBits), c);
-    node_records(bx, tr, r, c, m, A.mom64, A.mom32, A.wnode, A.cen64);
+    node_records(bx, tr, r, c, m, A.mom64, A.wnode, A.cen64);
     if (!(tr.corner & kLeafBit)) continue;
     const uint32_t f = tr.a, cnt = tr.b & kCountMask;
     for (uint32_t j = f; j < f + cnt; ++j) A.part32[j] = leaf_offset(A.part64[j], m, bx.Gf);
@@ -1864,13 +1863,13 @@ void launch_build(BuildArrays &A, hipStream_t s) {
     // grid-stride over nodes (the node count is known on the device only)
     const uint32_t gleaf = std::max<uint32_t>(1, std::min<uint32_t>(cdiv(A.node_cap, kThreads), 4096));
     k_moments_leaves<<<gleaf, kThreads, 0, s>>>(A.boxes, A.B, A.topo, A.parent, A.part64, A.part32, A.mom64,
-                                                A.mom32, A.wnode, A.cen64, A.scalars, A.node_cap, T, A.seps,
+                                                A.wnode, A.cen64, A.scalars, A.node_cap, T, A.seps,
                                                 A.semax, A.semin);
     const uint32_t gseg = std::max<uint32_t>(1, std::min<uint32_t>(cdiv(A.node_cap, kSegChunk), 4096));
     k_moments_segments<<<gseg, kThreads, 0, s>>>(A.boxes, A.B, A.topo, A.first, A.parent, A.top_id, A.mom64,
-                                                 A.mom32, A.wnode, A.cen64, A.scalars, A.node_cap, T, A.semax,
+                                                 A.wnode, A.cen64, A.scalars, A.node_cap, T, A.semax,
                                                  A.semin);
-    k_moments_top<<<1, kTopThreads, 0, s>>>(A.boxes, A.B, A.topo, A.first, A.mom64, A.mom32, A.wnode, A.cen64, T,
+    k_moments_top<<<1, kTopThreads, 0, s>>>(A.boxes, A.B, A.topo, A.first, A.mom64, A.wnode, A.cen64, T,
                                             A.semax, A.semin);
   }
 }

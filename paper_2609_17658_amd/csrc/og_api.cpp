@@ -116,19 +116,18 @@ void carve(Carver &c, BuildArrays &A, uint32_t n, uint32_t node_cap, int B, bool
   A.scan_partial = c.take<uint32_t>(std::max<size_t>(n, node_cap) / kScanTile + 4);
   A.topo = c.take<Topo>(node_cap);
   A.mom64 = c.take<Mom64>(node_cap);
-  A.mom32 = c.take<Mom32>(node_cap);
   A.wnode = c.take<WNode>(node_cap);
   A.cen64 = c.take<double4>(node_cap);
   A.first = c.take<uint32_t>(node_cap);
   A.skip = c.take<uint32_t>(node_cap);
   A.parent = c.take<uint32_t>(node_cap);
-  A.kid = c.take<uint32_t>(node_cap);
-  A.sib = c.take<uint32_t>(node_cap);
+  A.kid = c.take<uint32_t>(2ull * node_cap);
+  A.sib = A.kid ? A.kid + node_cap : nullptr;
   A.top_cap = top_node_bound(node_cap);
   A.top_cnt = c.take<uint32_t>(32);
   A.top_buf = c.take<uint32_t>(kTopWords * A.top_cap);
   A.top_id = c.take<uint32_t>(node_cap);
-  A.scalars = c.take<uint32_t>(kScalarWords);
+  A.scalars = c.take<uint32_t>(32);
   if (soft) {
     A.seps = c.take<double>(n);
     A.semax = c.take<double>(node_cap);
@@ -310,7 +309,6 @@ WalkArgs Forest::walk_args() const {
   WalkArgs W{};
   W.boxes = A.boxes;
   W.topo = A.topo;
-  W.mom32 = A.mom32;
   W.wnode = A.wnode;
   W.cen64 = A.cen64;
   W.mom64 = A.mom64;
@@ -330,7 +328,7 @@ WalkArgs Forest::walk_args() const {
     if (kind(b) != W.box_kind) W.box_kind = 0;
     if (b.spline || b.relative) W.ext = 1;
   }
-  W.counter = &A.scalars[32];
+  W.counter = A.digit_tot;
   W.group_lists = group_lists;
   W.seps = A.seps;
   W.semax = A.semax;
@@ -375,7 +373,7 @@ size_t subset_plan(TargetArrays &T, uint32_t M, char *base) {
   T.tval_b = c.take<uint32_t>(M);
   T.hist = c.take<uint32_t>(radix_hist_words(M));
   T.digit_tot = c.take<uint32_t>(256);
-  T.scalars = c.take<uint32_t>(kScalarWords);
+  T.scalars = c.take<uint32_t>(32);
   return c.off + 256;
 }
 
@@ -389,7 +387,7 @@ int Forest::walk_subset_in(int prec, hipStream_t s, const int64_t *idx, uint32_t
   WalkArgs W = walk_args();
   W.n_groups = (M + group_max - 1) / group_max;
   W.n_targets = M;
-  W.counter = &T.scalars[32];
+  W.counter = T.digit_tot;
   W.tkey = T.tkey;
   W.tval = T.tval;
   W.acc = acc;
@@ -427,7 +425,7 @@ int Forest::walk_active(int prec, hipStream_t s, const int8_t *bin, int32_t leve
     T.partial = cv.take<uint32_t>(scan_partial_words(N));
     T.tkey = cv.take<uint64_t>(N);
     T.tval = cv.take<uint32_t>(N);
-    T.counts = cv.take<uint32_t>(kScalarWords);
+    T.counts = cv.take<uint32_t>(32 + kQueueWords);
   };
   Carver c;
   plan(c);
@@ -515,7 +513,7 @@ constexpr uint32_t kNoAllocTargets = OG_NOALLOC_MAX_TARGETS;
 constexpr size_t noalloc_align(size_t x) { return (x + 255) & ~(size_t)255; }
 // the sizes subset_plan carves for M targets, each 256-byte aligned
 constexpr size_t noalloc_bytes(size_t M) {
-  const size_t parts[7] = {8 * M, 8 * M, 4 * M, 4 * M, 4 * 256 * ((M + kSortTile - 1) / kSortTile), 4 * 256, 4 * kScalarWords};
+  const size_t parts[7] = {8 * M, 8 * M, 4 * M, 4 * M, 4 * 256 * ((M + kSortTile - 1) / kSortTile), 4 * 256, 4 * 32};
   size_t off = 0;
   for (size_t p : parts) off = noalloc_align(off) + p;
   return off + 256;

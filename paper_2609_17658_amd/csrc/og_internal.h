@@ -72,13 +72,9 @@ struct __attribute__((aligned(16))) Topo {
   uint32_t b;
 };
 
-// Node moments: FP64 absolute centre of mass + mass; FP32 offset of the
-// centre of mass from the cube centre + mass.
+// Node moments: FP64 absolute centre of mass + mass.
 struct __attribute__((aligned(32))) Mom64 {
   double cx, cy, cz, m;
-};
-struct __attribute__((aligned(16))) Mom32 {
-  float ox, oy, oz, m;
 };
 
 // Walk record of a node for the mixed-precision walk, 48 bytes (scalar

@@ -41,17 +41,15 @@ struct BuildArrays {
   uint32_t *nstart, *S, *scan_partial;
   Topo *topo;
   Mom64 *mom64;
-  Mom32 *mom32;
   WNode *wnode;
   double4 *cen64;  // per node: FP64 cube centre (x, y, z) and side (w), for the FP64 walks
   uint32_t *first, *skip, *parent;
-  uint32_t *kid, *sib;        // per node: its child slots (k_links); the slots
+  uint32_t *kid, *sib;        // per node: its child slots (k_links); the slots (one array of 2 node_cap)
   uint32_t *top_cnt;          // [0] top nodes [1] child slots taken [2] deepest top level
   uint32_t *top_buf;          // TopArrays' lists, kTopWords per top node (top_cap)
   uint32_t *top_id;           // per node: index of a top node in the top list
   uint32_t top_cap;           // bound on the top nodes (top_node_bound)
-  uint32_t *scalars;          // [0] status [3] n_nodes [4] n [32..] walk queues (kScalarWords in all)
-                              // [5] deepest level (stats)
+  uint32_t *scalars;          // [0] status [3] n_nodes [4] n [5] deepest level (stats)
   int any_open;               // some box has periodic = 0
   int leaf_max;               // largest leaf_max of the boxes
   double *seps;               // sorted per-particle softening lengths (null: none given)
@@ -74,9 +72,12 @@ struct TopArrays {
   uint32_t cap;
 };
 // Walk group queues: one per XCD (see k_walk.hip), each counter on a cache
-// line of its own, after the 32 status and count words.
+// line of its own.  A tree's and a target list's stand in their digit_tot, which
+// is free once the sort is done (and which launch_walk resets), so that they
+// take no memory of their own.
 constexpr uint32_t kQueues = 8, kQueueStride = 32;
-constexpr uint32_t kScalarWords = 32 + kQueues * kQueueStride;
+constexpr uint32_t kQueueWords = kQueues * kQueueStride;
+static_assert(kQueueWords <= 256, "the counters fit digit_tot");
 
 constexpr size_t kTopWords = 20;  // words of top_buf per top node
 
@@ -91,7 +92,7 @@ struct TargetArrays {
   uint64_t *tkey_a, *tkey_b;
   uint32_t *tval_a, *tval_b;
   uint32_t *hist, *digit_tot;
-  uint32_t *scalars;          // [0] status [32..] walk queues (kScalarWords in all)
+  uint32_t *scalars;          // [0] status
   const uint64_t *tkey;       // result (points at a or b)
   const uint32_t *tval;
 };
@@ -108,7 +109,7 @@ struct ActiveArrays {
   uint32_t *partial;
   uint64_t *tkey;
   uint32_t *tval;
-  uint32_t *counts;           // [0] active, [1] groups, [32..] walk queues (kScalarWords in all)
+  uint32_t *counts;           // [0] active, [1] groups, [32..] walk queues (kQueueWords)
   int64_t *n_active;
 };
 void launch_active(const BuildArrays &A, ActiveArrays &T, uint32_t chunk, hipStream_t s);
@@ -117,7 +118,6 @@ size_t scan_partial_words(uint32_t n);
 struct WalkArgs {
   const BoxDev *boxes;
   const Topo *topo;
-  const Mom32 *mom32;
   const WNode *wnode;
   const double4 *cen64;
   const Mom64 *mom64;

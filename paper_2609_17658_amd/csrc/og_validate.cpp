@@ -85,7 +85,7 @@ extern "C" int og_tree_validate(const og_tree *tree) {
   std::vector<double4> part(N);
   std::vector<Topo> topo(nn);
   std::vector<Mom64> mom(nn);
-  std::vector<Mom32> m32(nn);
+  std::vector<uint32_t> kid(nn), sib(nn);
   std::vector<WNode> wn(nn);
   std::vector<double> seps, semax, semin;
   const bool soft = F.A.seps != nullptr;
@@ -106,7 +106,8 @@ extern "C" int og_tree_validate(const og_tree *tree) {
   cp(parent.data(), F.A.parent, 4ull * nn);
   cp(topo.data(), F.A.topo, sizeof(Topo) * nn);
   cp(mom.data(), F.A.mom64, sizeof(Mom64) * nn);
-  cp(m32.data(), F.A.mom32, sizeof(Mom32) * nn);
+  cp(kid.data(), F.A.kid, 4ull * nn);
+  cp(sib.data(), F.A.sib, 4ull * nn);
   cp(wn.data(), F.A.wnode, sizeof(WNode) * nn);
   if (soft) {
     cp(seps.data(), F.A.seps, 8ull * N);
@@ -223,6 +224,12 @@ extern "C" int og_tree_validate(const og_tree *tree) {
         if (ck.rc != OG_OK) break;
       }
       if (ck.rc == OG_OK && (kids < 1 || kids > 8)) ck.bad("node %u has %u children", r, kids);
+      // child slots: the children in this order (the root holds slot 0)
+      const uint32_t slot = kid[r] >> 3;
+      if (ck.rc == OG_OK && ((kid[r] & 7u) + 1u != kids || slot < 1 || slot + kids > nn || sib[0] != 0))
+        ck.bad("node %u has child slots %u of %u", r, slot, (kid[r] & 7u) + 1u);
+      for (uint32_t ch = r + 1, q = 0; ck.rc == OG_OK && q < kids; ch = skip[ch], ++q)
+        if (sib[slot + q] != ch) ck.bad("child slot %u of node %u holds %u, not %u", q, r, sib[slot + q], ch);
       if (ck.rc == OG_OK && next != f + cnt) ck.bad("children of node %u hold particles up to %u, not %u", r, next, f + cnt);
     }
     if (ck.rc != OG_OK) break;
@@ -238,8 +245,9 @@ extern "C" int og_tree_validate(const og_tree *tree) {
         if (!(std::fabs(com[k] - want) <= 1e-9 * side + 4.0 * tol * std::fabs(cen[k])))
           ck.bad("centre of mass of node %u is not its contents' (axis %d: %.17g vs %.17g)", r, k, com[k], want);
       }
-      if (std::fabs((double)m32[r].m - M) > 1e-6 * std::fabs(M)) ck.bad("FP32 mass of node %u", r);
-      const double o[3] = {m32[r].ox, m32[r].oy, m32[r].oz};
+      const float gm = bx.Gf * (float)mom[r].m;
+      if (wn[r].m != gm && gm == gm) ck.bad("FP32 mass of node %u", r);
+      const double o[3] = {wn[r].o[0], wn[r].o[1], wn[r].o[2]};
       for (int k = 0; k < 3; ++k)
         if (!(std::fabs(o[k] - (com[k] - cen[k])) <= 1e-6 * side)) ck.bad("FP32 offset of node %u", r);
     }
