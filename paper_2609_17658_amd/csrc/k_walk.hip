@@ -195,6 +195,14 @@ __device__ inline uint32_t range_begin(uint32_t n_groups, uint32_t q) {
   return (uint32_t)(((uint64_t)n_groups * q) / kQueues);
 }
 // Next group for this wave, or n_groups when all are taken.
+// kTight: a lane's counter address and range size, needed only once a range
+// is exhausted, are formed there (the empty asm) instead of being held in three
+// registers through the walk's loop.  For the kernels that have none to spare:
+// the extended group walk (81 registers, 5 waves per SIMD, or 78 and 6: 2M
+// particles with spline softening 8.45 | 7.92 ms) and the FP64 walks (three
+// spilled registers fewer).  The others have room and are up to 1.7 % faster
+// without (487k with spline and relative criterion).
+template <bool kTight = false>
 __device__ inline uint32_t pop_group(GroupQueue &Q, uint32_t lane) {
   while (true) {
     const uint32_t b = range_begin(Q.n_groups, Q.q), e = range_begin(Q.n_groups, Q.q + 1);
@@ -203,10 +211,12 @@ __device__ inline uint32_t pop_group(GroupQueue &Q, uint32_t lane) {
     i = __builtin_amdgcn_readlane(i, 0);  // wave-uniform
     if (b + i < e) return b + i;
     Q.done |= 1u << Q.q;  // each range is tried at most once more than it holds groups
+    uint32_t l = lane;
+    if (kTight) asm volatile("" : "+v"(l));
     bool left = false;
-    if (lane < kQueues) {
-      const uint32_t c = __hip_atomic_load(&Q.counters[lane * kQueueStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      left = c < range_begin(Q.n_groups, lane + 1) - range_begin(Q.n_groups, lane);
+    if (l < kQueues) {
+      const uint32_t c = __hip_atomic_load(&Q.counters[l * kQueueStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      left = c < range_begin(Q.n_groups, l + 1) - range_begin(Q.n_groups, l);
     }
     const uint32_t open = (uint32_t)__ballot(left) & ~Q.done;
     if (!open) return Q.n_groups;
@@ -590,7 +600,7 @@ __global__ __launch_bounds__(64 * kWalk64Waves) __attribute__((amdgpu_waves_per_
   if (A.n_groups == 0) return;
   GroupQueue Q = make_queue(A);
   while (true) {
-    const uint32_t g = pop_group(Q, lane);
+    const uint32_t g = pop_group<true>(Q, lane);
     if (g >= A.n_groups) break;
     const GroupRef gr = group_of(A, g);
     const BoxDev bx = ld(A.boxes + gr.box);
@@ -1369,7 +1379,7 @@ __global__ __launch_bounds__(kWalk32Threads) __attribute__((amdgpu_waves_per_eu(
   if (A.n_groups == 0) return;
   GroupQueue Q = make_queue(A);
   while (true) {
-    const uint32_t g = pop_group(Q, lane);
+    const uint32_t g = pop_group<true>(Q, lane);
     if (g >= A.n_groups) break;
     const GroupRef gr = group_of(A, g);
     const BoxDev bx = ld(A.boxes + gr.box);
@@ -2107,7 +2117,7 @@ __global__ __launch_bounds__(kWalk32Threads) __attribute__((amdgpu_waves_per_eu(
   if (A.n_groups == 0) return;
   GroupQueue Q = make_queue(A);
   while (true) {
-    const uint32_t g = pop_group(Q, lane);
+    const uint32_t g = pop_group<kExt>(Q, lane);
     if (g >= A.n_groups) break;
     const GroupRef gr = group_of(A, g);
     const BoxDev bx = ld(A.boxes + gr.box);
