@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "og_kernels.h"
+#include "og_lines.h"
 
 namespace og {
 
@@ -2314,26 +2315,13 @@ static bool env_flag(const char *name) {
 }
 static bool wide_nodes_forced() { return env_flag("OG_WIDE_NODES"); }
 
-// Up to how many targets the eight-lane walk takes (0: none).  It is faster
-// while the 64-target walks cannot fill the chip, and as long as its vector
-// loads and per-target tests cost less than their idle waves.  Measured
-// against them (clustered and smooth boxes, mixed | FP64, times as fast):
-//   all of     1k      32k     65k     100k    132k    160k    200k     300k     400k targets
-//   clustered  3.8|5.3 1.9|2.6 1.5|2.0 1.3|1.8 1.1     1.1|1.7 0.9|1.4  0.8|1.3  0.6|1.0
-//   smooth             2.9|3.4 2.2     1.6|1.7 1.2     1.1     0.95|1.1 0.9|1.06
-//   isolated   (20k) 2.3|4.7, (50k) 1.2|2.2, (70k) 1.0, (100k) 0.76|1.4, (200k) 0.5|0.9
-//   list of 2M         21|27 (1k)  2.7|3.0 (100k) 1.5|1.9 (200k) 1.2|1.6 (300k)
-//                      0.94|1.35 (400k) 0.7|1.0 (600k)
-// so the line lies at 160k (mixed) and 320k (FP64), lower without a cutoff
-// (no node is pruned, so a 64-target wave's lanes mostly agree), and twice as
-// high for lists of a quarter of the particles or less (whose targets lie
-// apart).  OG_EIGHT_MAX=n sets the line (the tests compare both sides); read
-// at each launch.
+// Up to how many targets the eight-lane walk takes (0: none).  OG_EIGHT_MAX=n
+// sets the line (the tests compare both sides); read at each launch.
 static uint32_t eight_lane_max(const WalkArgs &W, int precision) {
   if (!W.few || W.group_lists || wide_nodes_forced()) return 0;
   if (const char *e = getenv("OG_EIGHT_MAX")) return (uint32_t)atoi(e);
-  const uint32_t line = W.box_kind == 3 ? (precision == 0 ? 150000u : 70000u) : (precision == 0 ? 320000u : 160000u);
-  return std::max(line, std::min(2 * line, W.n_particles / 4));
+  const WalkShape shape{precision == 0, W.box_kind == 3, W.ext != 0, W.relative != 0, W.leaf_max, W.theta, W.alpha};
+  return eight_lane_line(shape, W.tkey != nullptr, W.n_particles);
 }
 
 void launch_walk(const WalkArgs &W0, int precision, hipStream_t s) {

@@ -324,9 +324,17 @@ WalkArgs Forest::walk_args() const {
   W.B = B;
   auto kind = [](const BoxDev &b) { return b.cutoff ? (b.periodic ? 2 : 1) : 3; };
   W.box_kind = kind(hboxes[0]);
+  W.leaf_max = hboxes[0].leaf_max;
+  W.theta = W.alpha = INFINITY;
   for (const auto &b : hboxes) {
     if (kind(b) != W.box_kind) W.box_kind = 0;
     if (b.spline || b.relative) W.ext = 1;
+    if (b.relative) {
+      W.relative = 1;
+      W.alpha = std::min(W.alpha, b.alpha);
+    }
+    W.leaf_max = std::min<int>(W.leaf_max, b.leaf_max);
+    W.theta = std::min(W.theta, std::sqrt(b.theta2));
   }
   W.counter = A.digit_tot;
   W.group_lists = group_lists;

@@ -148,6 +148,8 @@ struct WalkArgs {
   uint32_t n_particles;       // particles of the forest
   uint32_t small_max;         // walks of up to this many targets are eight-lane walks (set by launch_walk)
   int few;                    // 1: every array within 4 GiB, so the eight-lane walk may run
+  int leaf_max, relative;     // smallest leaf_max of the boxes; a box with the relative criterion
+  double theta, alpha;        // smallest of the boxes
   int wide_nodes;             // the node records span more than 4 GiB (64-bit record offsets)
   int no_interior;            // mixed walk: reduce every periodic offset (no raw form for interior groups)
   int erfc_tail;              // FP64 walks: some box has r_cut / (2 r_s) >= 3 (library erfc past the polynomial)
