@@ -127,7 +127,7 @@ typedef struct og_params {
                                with OG_LISTS_GROUP) */
     int32_t walk_list_cap;  /* mixed walk: accepted partners buffered per
                                target before evaluation, 4, 8, 16 or 32; 0 =
-                               default (4; a fifth where it costs no wave);
+                               default (4 with per-particle lengths, else 5);
                                the result does not depend on it */
     int32_t softening;      /* OG_SOFT_PLUMMER (default) or OG_SOFT_SPLINE
                                (needs eps > 0) */

@@ -2296,12 +2296,13 @@ __global__ __launch_bounds__(kWalk32Threads) __attribute__((amdgpu_waves_per_eu(
 
 }  // namespace
 
+// List entries when the caller names none (0: the walk's own choice).
 int walk_list_capacity() {
   static int cap = -1;
   if (cap < 0) {
     const char *e = getenv("OG_WALK_LIST_CAP");
     const int v = e ? atoi(e) : 0;
-    cap = (v == 4 || v == 8 || v == 16 || v == 32) ? v : 4;
+    cap = (v == 4 || v == 8 || v == 16 || v == 32) ? v : 0;
   }
   return cap;
 }
@@ -2385,12 +2386,13 @@ void launch_walk(const WalkArgs &W0, int precision, hipStream_t s) {
     else if (W.erfc_tail) k_walk64<false, true><<<blocks, 64 * kWalk64Waves, 0, s>>>(W);
     else k_walk64<false, false><<<blocks, 64 * kWalk64Waves, 0, s>>>(W);
   } else {
-    // one wave per workgroup; LDS per wave = cap x 1 KB of lists.  The shortest
-    // lists (4) get a fifth entry where no softening lengths are listed: 32
-    // waves of 5 KB are exactly a CU's LDS, and fuller rows of the evaluation
-    // cost no wave (16.8M Zel'dovich particles 17.2 -> 16.9 ms, 2M mixture the
-    // same; 6 entries at 6 waves lose 10 %).
-    const int cap = W.list_cap > 0 ? W.list_cap : walk_list_capacity();
+    // one wave per workgroup; LDS per wave = cap x 1 KB of lists.  Unless the
+    // caller names a depth, lists of 4, with a fifth entry where no softening
+    // lengths are listed: 32 waves of 5 KB are exactly a CU's LDS, and fuller
+    // rows of the evaluation cost no wave (16.8M Zel'dovich particles 17.2 ->
+    // 16.9 ms, 2M mixture the same; 6 entries at 6 waves lose 10 %).
+    const int named = W.list_cap > 0 ? W.list_cap : walk_list_capacity();
+    const int cap = named > 0 ? named : 5;
     const uint32_t per_cu = std::min<uint32_t>(32u, 160u / (uint32_t)cap);
     const uint32_t blocks = std::max<uint32_t>(1, std::min<uint32_t>(per_cu * cus, groups));
     const int mode = W.box_kind;
@@ -2407,7 +2409,8 @@ void launch_walk(const WalkArgs &W0, int precision, hipStream_t s) {
     else k_walk32<C, 0, false><<<blocks, kWalk32Threads, 0, s>>>(W);                 \
   } while (0)
     if (cap == 8) OG_WALK32(8);
-    else if (cap == 4) OG_WALK32(5);
+    else if (cap == 5) OG_WALK32(5);
+    else if (cap == 4) OG_WALK32(4);
     else if (cap == 32) OG_WALK32(32);
     else OG_WALK32(16);
 #undef OG_WALK32

@@ -23,7 +23,8 @@ import math
 import os
 import time
 
-DEFAULT_SPACE = {"group_max": [32, 64], "walk_list_cap": [4, 8], "leaf_max": [8, 16]}
+# walk_list_cap 0: the library's own depth (4 or 5)
+DEFAULT_SPACE = {"group_max": [32, 64], "walk_list_cap": [0, 8], "leaf_max": [8, 16]}
 
 
 def time_batch(items, group_max=64, walk_list_cap=4, leaf_max=None, precision="mixed", reps=3,
@@ -76,7 +77,7 @@ def tune_batch(items, space=None, precision="mixed", reps=3, log=None):
     return {"best": best, "trials": trials, "seconds": time.time() - t0}
 
 
-TREE_SPACE = {"group_max": [32, 64], "walk_list_cap": [4, 8], "leaf_max": [4, 8, 16]}
+TREE_SPACE = {"group_max": [32, 64], "walk_list_cap": [0, 8], "leaf_max": [4, 8, 16]}
 
 
 def time_tree(pos, mass, box, params, group_max=64, walk_list_cap=4, leaf_max=None, precision="mixed",

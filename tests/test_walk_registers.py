@@ -52,8 +52,16 @@ def kernels(tmp_path_factory):
     ("k_walk64s<0, false, 4, false>", 7, 2), ("k_walk64s<0, false, 4, true>", 6, 22), ("k_walk64<false, true>", 4, 13),
     ("k_walk8<true, false, false>", 5, 0),
     ("k_walk8<false, false, false>", 5, 0), ("k_walk32<5, 2, false, false, false>", 8, 0),
-    ("k_walk32<4, 0, true, true, false>", 8, 0)])
+    ("k_walk32<4, 0, true, true, false>", 8, 0), ("k_walk32<4, 2, false, false, false>", 8, 0)])
 def test_waves_and_spills(kernels, name, waves, spills):
     vgprs, spilled = kernels[name]
     assert 512 // (-(-vgprs // 8) * 8) >= waves, (vgprs, spilled)
     assert spilled <= spills
+
+
+def test_list_depths_are_built(kernels):
+    """Every depth that walk_list_cap names has its own walk of each kind of box
+    (a depth of 4 is not another one's)."""
+    for cap in (4, 5, 8, 16, 32):
+        for mode in range(4):
+            assert "k_walk32<%d, %d, false, false, false>" % (cap, mode) in kernels
