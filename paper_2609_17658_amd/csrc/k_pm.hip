@@ -28,6 +28,7 @@
 #include <cstdlib>
 
 #include "og_kernels.h"
+#include "og_lines.h"
 #include "og_pm.h"
 
 namespace og {
@@ -1198,17 +1199,14 @@ void launch_fft_pass(double2 *data, const PmTables &Tb, int n, int logn, int sig
 struct BinScratch {
   uint64_t *keys_a, *keys_b;
   uint32_t *vals_a, *vals_b, *hist, *digit_tot;
-  // Whether this call takes it: enough particles that eight atomics each cost
-  // more than the sort, and room for it in B.  Measured (whole call, us,
-  // atomics|blocks): clustered particles in random order on 256^3 1143|1030 at
-  // 5e5, 2131|1356 at 2.1e6, on 128^3 465|295 at 4e5, 908|399 at 1e6; grid
-  // order, whose atomics mostly hit one line per wave, on 256^3 1011|979 at
-  // 4.9e5, 1207|1098 at 2.1e6, on 128^3 218|234 at 4e5, 256|262 at 1e6; below
-  // 5e5 the launches cost grid-ordered particles more than the atomics (86|135
-  // at 1.5e5 on 64^3).  OG_PM_BIN_MIN=n sets the line (the tests compare both).
+  // Whether this call takes it: enough particles (block_deposit_line) and room
+  // for them in B: 24.3 bytes of scratch a particle in 16 bytes a cell, so up to
+  // 1.38M particles on 128^3, 11M on 256^3, and never on 64^3 and below, whose
+  // 173 thousand are under the line; a call past it takes the atomics.
+  // OG_PM_BIN_MIN=n sets the line (the tests compare both).
   bool place(const PmArgs &P, uint64_t cells) {
     const char *e = getenv("OG_PM_BIN_MIN");
-    if (P.N < (e ? (uint32_t)atoi(e) : 500000u)) return false;
+    if (P.N < (e ? (uint64_t)(uint32_t)atoi(e) : block_deposit_line(P.n))) return false;
     char *base = reinterpret_cast<char *>(P.B);
     size_t off = 0;
     auto take = [&](size_t bytes) {

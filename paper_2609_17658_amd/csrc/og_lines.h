@@ -1,5 +1,4 @@
-// Up to how many targets a walk takes eight lanes per target (k_walk8) instead
-// of one (the 64-target walks).  Host code only.
+// Lines between two ways of doing the same work, measured.  Host code only.
 #pragma once
 
 #include <algorithm>
@@ -19,7 +18,8 @@ struct WalkShape {
   double theta, alpha;
 };
 
-// Eight lanes per target are faster while the 64-target walks cannot fill the
+// Up to how many targets a walk takes eight lanes per target (k_walk8) instead of
+// one (the 64-target walks).  Eight lanes are faster while the 64-target walks cannot fill the
 // chip, and as long as their vector loads and per-target tests cost less than
 // those walks' idle waves.  Measured, 64-target walk time / eight-lane time
 // (mixed | FP64), theta 0.5, leaves of 8:
@@ -78,5 +78,17 @@ inline uint32_t eight_lane_line(const WalkShape &w, bool list, uint32_t n_partic
   }
   return (uint32_t)std::max(0.0, line);
 }
+
+// From how many caller-order particles the mesh deposit goes by blocks of 8^3
+// cells (the particles' numbers sorted by block first) instead of eight atomics a
+// particle, on a mesh of n^3 cells.  Measured, whole call, us, atomics|blocks:
+// clustered particles in random order on 256^3 1117|1037 at 5e5, 1953|1347 at
+// 2e6, on 128^3 522|309 at 4e5, 1046|404 at 1e6, on 512^3 8322|8642 at 1e6,
+// 8939|8910 at 2e6, 9584|9194 at 3e6; grid order, whose atomics mostly hit one
+// line per wave, on 256^3 946|980 at 5.1e5, 1032|1018 at 1e6, on 128^3 229|241
+// at 5.1e5, 263|259 at 1e6, on 512^3 8123|8524 at 1e6, 8378|8682 at 2.1e6,
+// 8666|8898 at 3.4e6.  A block's own cost (its nodes stored, its halo written and
+// read) does not shrink with its particles, so a large mesh needs more of them.
+inline uint64_t block_deposit_line(uint64_t n) { return std::max<uint64_t>(500000, n * n * n / 32); }
 
 }  // namespace og
