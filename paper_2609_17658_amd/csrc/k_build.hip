@@ -282,23 +282,24 @@ __global__ __launch_bounds__(kThreads) void k_keys(const BoxDev *boxes, int B, u
 }
 
 // ---------------------------------------------------------------- sort --
-constexpr int kSortItems = kSortTile / kThreads;  // 16 per thread
-
 __device__ inline uint32_t sort_digit(uint64_t key, uint32_t val, int pass, const BoxDev *boxes,
                                       int B) {
   if (pass < 8) return (uint32_t)(key >> (8 * pass)) & 255u;
   return ((uint32_t)box_of(boxes, B, val) >> (8 * (pass - 8))) & 255u;
 }
 
+// kTile: keys a workgroup takes, 4096, or 1024 for the mesh's short keys (see
+// BinScratch): then a sort of 5e5 keys has 489 workgroups instead of 122.
+template <uint32_t kTile>
 __global__ __launch_bounds__(kThreads) void k_sort_hist(const uint64_t *keys, const uint32_t *vals,
                                                         uint32_t n, int pass, const BoxDev *boxes,
                                                         int B, uint32_t *hist, uint32_t ntiles) {
   __shared__ uint32_t h[256];
   h[threadIdx.x] = 0;
   __syncthreads();
-  const uint32_t base = blockIdx.x * kSortTile;
+  const uint32_t base = blockIdx.x * kTile;
 #pragma unroll 4
-  for (int r = 0; r < kSortItems; ++r) {
+  for (int r = 0; r < (int)(kTile / kThreads); ++r) {
     uint32_t e = base + r * kThreads + threadIdx.x;
     // the key passes need no value
     if (e < n) atomicAdd(&h[sort_digit(keys[e], pass < 8 ? 0u : vals[e], pass, boxes, B)], 1u);
@@ -324,26 +325,28 @@ __global__ __launch_bounds__(kThreads) void k_sort_rowscan(uint32_t *hist, uint3
   if (threadIdx.x == 0) digit_tot[blockIdx.x] = carry;
 }
 
-// Stable scatter of one tile.  Wave w owns tile elements
-// [w*1024, (w+1)*1024) in 16 rounds of 64; ranks among equal digits come
+// Stable scatter of one tile.  Wave w owns the tile's w-th quarter, in rounds of
+// 64; ranks among equal digits come
 // from ballot-matched peer masks, per-wave running counts, a scan over
 // waves and a scan over digits.  The tile is reordered in LDS first so that
 // the global writes of each digit run are contiguous.
+template <uint32_t kTile>
 __global__ __launch_bounds__(kThreads) void k_sort_scatter(const uint64_t *keys_in, const uint32_t *vals_in,
                                                            uint64_t *keys_out, uint32_t *vals_out,
                                                            uint32_t n, int pass, const BoxDev *boxes,
                                                            int B, const uint32_t *hist,
                                                            const uint32_t *digit_tot, uint32_t ntiles) {
-  __shared__ uint64_t skeys[kSortTile];
-  __shared__ uint32_t svals[kSortTile];
+  constexpr int kSortItems = kTile / kThreads;
+  __shared__ uint64_t skeys[kTile];
+  __shared__ uint32_t svals[kTile];
   __shared__ uint32_t wcnt[kWaves][256];
   __shared__ uint32_t gbase[256];    // global base of each digit for this tile
   __shared__ uint32_t tbase[256];    // base of each digit inside the tile
   __shared__ uint32_t tmp[kWaves];
 
   const uint32_t tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
-  const uint32_t base = blockIdx.x * kSortTile;
-  const uint32_t tile_n = min(kSortTile, n - base);
+  const uint32_t base = blockIdx.x * kTile;
+  const uint32_t tile_n = min(kTile, n - base);
 
   // digit bases over the whole array: exclusive scan of the digit totals
   {
@@ -1728,25 +1731,33 @@ void launch_max_level(const BuildArrays &A, uint32_t *out, hipStream_t s) {
   k_max_level<<<g, kThreads, 0, s>>>(A.topo, A.scalars, A.node_cap, out);
 }
 
-size_t radix_hist_words(uint32_t n) { return (size_t)256 * cdiv(n > 0 ? n : 1, kSortTile); }
+size_t radix_hist_words(uint32_t n, uint32_t tile) { return (size_t)256 * cdiv(n > 0 ? n : 1, tile); }
 
-bool radix_sort(uint64_t *keys_a, uint32_t *vals_a, uint64_t *keys_b, uint32_t *vals_b, uint32_t n,
-                int pass_lo, int pass_hi, int box_passes, const BoxDev *boxes, int B,
-                uint32_t *hist, uint32_t *digit_tot, hipStream_t s) {
-  const uint32_t ntiles = cdiv(n, kSortTile);
+template <uint32_t kTile>
+static bool radix_sort_tiles(uint64_t *keys_a, uint32_t *vals_a, uint64_t *keys_b, uint32_t *vals_b, uint32_t n,
+                             int pass_lo, int pass_hi, int box_passes, const BoxDev *boxes, int B, uint32_t *hist,
+                             uint32_t *digit_tot, hipStream_t s) {
+  const uint32_t ntiles = cdiv(n, kTile);
   uint64_t *ki = keys_a, *ko = keys_b;
   uint32_t *vi = vals_a, *vo = vals_b;
   bool in_b = false;
   for (int pass = pass_lo; pass < pass_hi + box_passes; ++pass) {
     const int pp = pass < pass_hi ? pass : 8 + (pass - pass_hi);
-    k_sort_hist<<<ntiles, kThreads, 0, s>>>(ki, vi, n, pp, boxes, B, hist, ntiles);
+    k_sort_hist<kTile><<<ntiles, kThreads, 0, s>>>(ki, vi, n, pp, boxes, B, hist, ntiles);
     k_sort_rowscan<<<256, kThreads, 0, s>>>(hist, ntiles, digit_tot);
-    k_sort_scatter<<<ntiles, kThreads, 0, s>>>(ki, vi, ko, vo, n, pp, boxes, B, hist, digit_tot, ntiles);
+    k_sort_scatter<kTile><<<ntiles, kThreads, 0, s>>>(ki, vi, ko, vo, n, pp, boxes, B, hist, digit_tot, ntiles);
     std::swap(ki, ko);
     std::swap(vi, vo);
     in_b = !in_b;
   }
   return in_b;
+}
+
+bool radix_sort(uint64_t *keys_a, uint32_t *vals_a, uint64_t *keys_b, uint32_t *vals_b, uint32_t n,
+                int pass_lo, int pass_hi, int box_passes, const BoxDev *boxes, int B,
+                uint32_t *hist, uint32_t *digit_tot, hipStream_t s, uint32_t tile) {
+  return (tile == kSortTile ? radix_sort_tiles<kSortTile> : radix_sort_tiles<kSortTile / 4>)(
+      keys_a, vals_a, keys_b, vals_b, n, pass_lo, pass_hi, box_passes, boxes, B, hist, digit_tot, s);
 }
 
 // An environment switch that is set to 1 (the tests compare both sides).

@@ -1196,13 +1196,23 @@ void launch_fft_pass(double2 *data, const PmTables &Tb, int n, int logn, int sig
 }  // namespace
 
 // Scratch of the caller-order deposit by blocks, carved from B.
+constexpr uint32_t kSmallTiles = 1200000;
 struct BinScratch {
   uint64_t *keys_a, *keys_b;
   uint32_t *vals_a, *vals_b, *hist, *digit_tot;
+  uint32_t tile;  // keys per workgroup of the sort
   // Whether this call takes it: enough particles (block_deposit_line) and room
   // for them in B: 24.3 bytes of scratch a particle in 16 bytes a cell, so up to
   // 1.38M particles on 128^3, 11M on 256^3, and never on 64^3 and below, whose
   // 173 thousand are under the line; a call past it takes the atomics.
+  // Up to kSmallTiles particles the sort takes tiles of 1024 keys: 4096 leave it
+  // half the chip (two scatters of 15 us each at 5e5 particles), which made the
+  // call slower than the atomics for particles in grid order.  Whole call, us,
+  // atomics | tiles of 4096 | of 1024: grid order on 128^3 229|241|224 at 5.1e5,
+  // 263|259|254 at 1e6, on 256^3 946|980|964, 1032|1018|1009; clustered on 256^3
+  // 1117|1037|1022 at 5e5, 1400|1131|1122 at 1e6.  From 2e6 on 4096 are faster
+  // (1156|1103|1115), and the small tiles' histogram would take the room of
+  // 4 % of the particles.
   // OG_PM_BIN_MIN=n sets the line (the tests compare both).
   bool place(const PmArgs &P, uint64_t cells) {
     const char *e = getenv("OG_PM_BIN_MIN");
@@ -1218,7 +1228,8 @@ struct BinScratch {
     keys_b = reinterpret_cast<uint64_t *>(take(8ull * P.N));
     vals_a = reinterpret_cast<uint32_t *>(take(4ull * P.N));
     vals_b = reinterpret_cast<uint32_t *>(take(4ull * P.N));
-    hist = reinterpret_cast<uint32_t *>(take(4 * radix_hist_words(P.N)));
+    tile = P.N <= kSmallTiles ? kSortTile / 4 : kSortTile;
+    hist = reinterpret_cast<uint32_t *>(take(4 * radix_hist_words(P.N, tile)));
     digit_tot = reinterpret_cast<uint32_t *>(take(4 * 256));
     return off <= cells * sizeof(double2);
   }
@@ -1262,7 +1273,7 @@ void launch_pm(const PmArgs &P, hipStream_t s) {
     int passes = 1;
     while (((uint64_t)(nblocks - 1) >> (8 * passes)) != 0) ++passes;
     const bool in_b = radix_sort(bin.keys_a, bin.vals_a, bin.keys_b, bin.vals_b, P.N, 0, passes, 0, nullptr, 1, bin.hist,
-                                 bin.digit_tot, s);
+                                 bin.digit_tot, s, bin.tile);
     BlockRef RB{in_b ? bin.keys_b : bin.keys_a, P.bstart, 0, kCurveRows, 0.0};
     PartRef RP = R;
     RP.ord = in_b ? bin.vals_b : bin.vals_a;

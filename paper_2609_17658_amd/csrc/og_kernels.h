@@ -13,12 +13,13 @@ constexpr uint32_t kScanTile = 4096;
 // LSD radix sort of (key, val) pairs, 8-bit digits.  Key passes
 // [pass_lo, pass_hi) on the 64-bit key, then `box_passes` passes on the box
 // of each value (global particle index).  Ping-pongs between a and b;
-// returns true when the result ends in b.
+// returns true when the result ends in b.  `tile`: keys per workgroup, kSortTile
+// or a quarter of it; `hist` holds radix_hist_words(n, tile) words.
 constexpr uint32_t kSortTile = 4096;
 bool radix_sort(uint64_t *keys_a, uint32_t *vals_a, uint64_t *keys_b, uint32_t *vals_b,
                 uint32_t n, int pass_lo, int pass_hi, int box_passes, const BoxDev *boxes,
-                int B, uint32_t *hist, uint32_t *digit_tot, hipStream_t s);
-size_t radix_hist_words(uint32_t n);
+                int B, uint32_t *hist, uint32_t *digit_tot, hipStream_t s, uint32_t tile = kSortTile);
+size_t radix_hist_words(uint32_t n, uint32_t tile = kSortTile);
 
 // Tile of the merge sort that small boxes and target lists take.
 constexpr uint32_t kMergeTile = 1024;

@@ -89,6 +89,6 @@ inline uint32_t eight_lane_line(const WalkShape &w, bool list, uint32_t n_partic
 // at 5.1e5, 263|259 at 1e6, on 512^3 8123|8524 at 1e6, 8378|8682 at 2.1e6,
 // 8666|8898 at 3.4e6.  A block's own cost (its nodes stored, its halo written and
 // read) does not shrink with its particles, so a large mesh needs more of them.
-inline uint64_t block_deposit_line(uint64_t n) { return std::max<uint64_t>(500000, n * n * n / 32); }
+inline uint64_t block_deposit_line(uint64_t n) { return std::max<uint64_t>(500000, n * n * n / 34); }
 
 }  // namespace og

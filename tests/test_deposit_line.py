@@ -30,3 +30,16 @@ def test_line(tmp_path):
     for (mesh, n, atomics, blocks), line in zip(MEASURED, out):
         if n >= int(line):  # by blocks: at most 2 % slower
             assert blocks <= 1.02 * atomics, (mesh, n, line)
+
+
+def test_sort_of_half_a_million_keys_fills_the_chip():
+    """Around the line the sort by blocks has at least a workgroup per compute
+    unit (256): with 4096 keys each it had 122, and the call was slower than the
+    atomics for particles in grid order."""
+    def constant(name, source):
+        text = open(os.path.join(CSRC, source)).read()
+        return int(text.split("constexpr uint32_t %s = " % name)[1].split(";")[0])
+    tile, small = constant("kSortTile", "og_kernels.h"), constant("kSmallTiles", "k_pm.hip")
+    assert 500000 <= small
+    for n in (500000, small, small + 1, 2097152):
+        assert -(-n // (tile // 4 if n <= small else tile)) >= 256, n
