@@ -2353,6 +2353,13 @@ void launch_walk(const WalkArgs &W0, int precision, hipStream_t s) {
     return;
   }
   W.small_max = env_flag("OG_WALK64_PLAIN") && precision == 0 ? 0u : eight_lane_max(W, precision);
+  // The mixed 64-target walk tells a listed leaf from a monopole by the sign of
+  // G m, so a negative G takes the eight-lane walk at any size, and the FP64 one
+  // where that cannot run.
+  if (W.negative && precision != 0) {
+    if (W.few && !wide_nodes_forced()) W.small_max = 0xffffffffu;
+    else precision = 0;
+  }
   const uint32_t most = W.n_targets;  // of a list made on the device: a bound
   if (W.small_max > 0 && (W.dev_count || most <= W.small_max)) {
     // one wave per workgroup; registers and LDS allow 18 (FP64: 20) per CU

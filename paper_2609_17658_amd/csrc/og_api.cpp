@@ -333,6 +333,7 @@ WalkArgs Forest::walk_args() const {
       W.relative = 1;
       W.alpha = std::min(W.alpha, b.alpha);
     }
+    if (std::signbit(b.Gf)) W.negative = 1;
     W.leaf_max = std::min<int>(W.leaf_max, b.leaf_max);
     W.theta = std::min(W.theta, std::sqrt(b.theta2));
   }

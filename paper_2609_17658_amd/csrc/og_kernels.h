@@ -158,6 +158,7 @@ struct WalkArgs {
   int few;                    // 1: every array within 4 GiB, so the eight-lane walk may run
   int leaf_max, relative;     // smallest leaf_max of the boxes; a box with the relative criterion
   double alpha;               // smallest of the boxes (relative criterion)
+  int negative;               // some box's G carries a minus sign
   int wide_nodes;             // the node records span more than 4 GiB (64-bit record offsets)
   int no_interior;            // mixed walk: reduce every periodic offset (no raw form for interior groups)
   int erfc_tail;              // FP64 walks: some box has r_cut / (2 r_s) >= 3 (library erfc past the polynomial)
