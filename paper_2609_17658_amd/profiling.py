@@ -9,6 +9,8 @@
       the particle-mesh force of the same mixture on a 256^3 mesh;
   python paper_2609_17658_amd/profiling.py pmtree --n-grid 256 --reps 3
       the same from a built tree (og_pm_force_tree, curve order);
+  python paper_2609_17658_amd/profiling.py case --name step_32k_fp64 --reps 3
+      one of the listed cases of perf/cases.py, `reps` passes;
   python paper_2609_17658_amd/profiling.py copy --mib 1024 --reps 3
       device-to-device copy of a buffer of known size, the reference for
       scaling FETCH_SIZE / WRITE_SIZE readings to bytes.
@@ -99,6 +101,19 @@ def _pm_tree(n_grid: int, reps: int, workload: str):
     print("pm from the tree %d^3 x%d on %s: done" % (n_grid, reps, workload), flush=True)
 
 
+def _case(name: str, reps: int):
+    import torch
+
+    from perf import cases
+
+    case = next(c for c in cases.listed() if c["name"] == name)
+    state = cases.prepare(case, 7)
+    for _ in range(reps):
+        cases.run(state)
+    torch.cuda.synchronize()
+    print("case %s x%d: done" % (name, reps), flush=True)
+
+
 def _copy(mib: int, reps: int):
     import torch
 
@@ -129,6 +144,9 @@ def main(argv=None):
     mt.add_argument("--n-grid", type=int, default=256)
     mt.add_argument("--reps", type=int, default=3)
     mt.add_argument("--workload", default="mixture2m")
+    ca = sub.add_parser("case")
+    ca.add_argument("--name", required=True)
+    ca.add_argument("--reps", type=int, default=3)
     c = sub.add_parser("copy")
     c.add_argument("--mib", type=int, default=1024)
     c.add_argument("--reps", type=int, default=3)
@@ -141,6 +159,8 @@ def main(argv=None):
         _pm(a.n_grid, a.reps, a.workload)
     elif a.cmd == "pmtree":
         _pm_tree(a.n_grid, a.reps, a.workload)
+    elif a.cmd == "case":
+        _case(a.name, a.reps)
     else:
         _copy(a.mib, a.reps)
     return 0
