@@ -52,14 +52,18 @@ inline uint32_t eight_lane_line(const WalkShape &w, bool list, uint32_t n_partic
   // how far theta lies below 0.45, up to where the line stops falling
   const double below = w.relative ? 0.0 : std::max(0.0, 0.45 - w.theta);
   const double d = std::min(below, w.fp64 ? 0.3 : 0.25);
+  const double e = w.relative ? 0.0 : std::min(0.17, std::max(0.0, 0.4 - w.theta));  // mixed walks with a cutoff
   const double base = w.newton ? (w.fp64 ? 150e3 : 70e3) : (w.fp64 ? 320e3 : 160e3);
-  double f;  // the line of a whole box, of `base`
-  if (w.relative) f = w.fp64 ? 1.0 - 0.015 * k : 1.0 - (w.alpha < 0.001 ? 0.18 : 0.1) * std::max(0.0, k - 1.0);
+  // The line of a whole box as a share of `base`: straight lines through the times
+  // above, in theta and in halvings of the leaf size (k).
+  double f;
+  if (w.relative && w.fp64) f = 1.0 - 0.015 * k;
+  else if (w.relative) f = 1.0 - (w.alpha < 0.001 ? 0.18 : w.alpha < 0.005 ? 0.1 : 0.0) * std::max(0.0, k - 1.0);
   else if (w.newton && w.ext) f = 1.0 - (w.fp64 ? 0.27 : 0.3) * k * d;
   else if (w.ext) f = w.fp64 ? 1.0 - k * (0.01 + 0.2 * d) : 1.0 - k * d;
-  else if (w.fp64) f = 1.0 - k * ((w.newton ? 0.035 : 0.008) + 0.87 * d);
+  else if (w.fp64) f = 1.0 - k * (w.newton ? 0.035 + 0.68 * d : 0.008 + 0.87 * d);
   else if (w.newton) f = w.leaf_max == 1 && w.theta < 0.15 ? 0.0 : 1.0 - d * (1.5 + 0.1 * k);
-  else f = 1.0 - d * (1.5 + 0.6 * k);
+  else f = 1.0 - 0.004 * k - e * (2.0 + 0.9 * k);
   double line = base * f;
   if (list) {
     const double quarter = n_particles / 4;
@@ -71,9 +75,9 @@ inline uint32_t eight_lane_line(const WalkShape &w, bool list, uint32_t n_partic
     } else if (w.fp64) {
       line = std::max(line, std::min(2.0 * base * (1.0 - d * (0.7 + 0.65 * k)), quarter * (1.0 - 0.6 * k * d)));
     } else {
-      const double all = base * (1.0 - d * (1.1 + 0.3 * k));  // of a list whatever the box
+      const double all = base * (1.0 - e * (1.4 + 0.45 * k));  // of a list whatever the box
       const double far = std::min(below, 0.3);
-      line = std::max({line, all, std::min(2.0 * base * (1.0 - 8.5 * far * far), quarter * (1.0 - d * (1.2 + 0.35 * k)))});
+      line = std::max({line, all, std::min(2.0 * base * (1.0 - 8.5 * far * far), quarter * (1.0 - e * (1.9 + 0.55 * k)))});
     }
   }
   return (uint32_t)std::max(0.0, line);
